@@ -81,7 +81,9 @@ typedef struct gd_ctx gd_ctx;
  *     the sequence non-decreasing (empty tensors are allowed) and
  *     N = tensor_offsets[T] at most 2^32 - 2 (indices are sent as uint32).
  *   Allocates all device scratch on the current HIP device (about 16 bytes
- *   per element plus about 135 KB per tensor for the per-tensor histograms);
+ *   per element plus about 135 KB per tensor for the per-tensor histograms, and
+ *   for layouts of at most 6,291,456 elements another 128 KB per tensor, or
+ *   16 KB where there are more than 1,024 tensors);
  *   gd_compress never allocates.  Any number of tensors is accepted.
  *   Returns GD_ERR_LAYOUT for a bad layout, GD_ERR_OOM when allocation fails.
  */
@@ -272,7 +274,7 @@ gd_status gd_apply_quantised(gd_ctx* ctx, float* params, uint32_t num_pushes, co
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  It takes the layout per call instead of a gd_ctx and
  * allocates nothing (no device or host allocation, no memset); its kernels
- * use a fixed 48 MiB scratch array compiled into the library, one copy per
+ * use a fixed 24 MiB scratch array compiled into the library, one copy per
  * GPU, held from the first call on that GPU until the process ends.
  *   tensor_offsets (host, num_tensors + 1 entries): as gd_create, with at
  *     most 64 tensors and N = tensor_offsets[num_tensors] <= 2,097,152
@@ -314,7 +316,9 @@ gd_status gd_profile_read(gd_ctx* ctx, double* dense_ms, uint64_t* dense_launche
 
 /*
  * Test hook: override the sampled threshold bracket of later gd_compress
- * calls on this ctx, to exercise paths that real samples rarely take.  The
+ * calls on this ctx, to exercise paths that real samples rarely take (a mode
+ * other than 0 also keeps small layouts, which would read every element in
+ * every pass instead of sampling, on the sampled path).  The
  * results do not change (they are exact whatever the bracket); only the
  * work done does.  mode 0: normal; 1: bracket above every key, so every
  * segment takes the exact fallback; 2: the dense pass zeroes every

@@ -111,10 +111,62 @@ bool set_columns(gd_ctx* ctx, const std::vector<uint32_t>& columns) {
     return true;
 }
 
+// The events of the launch that streams grad and residual, where it is one
+// that gd_profile_enable asked to time.
+struct DenseTimer {
+    hipEvent_t t0 = nullptr, t1 = nullptr;
+    explicit DenseTimer(const gd_ctx* ctx) {
+        if (ctx->profile_every == 0 || ctx->dense_launches % ctx->profile_every != 0 ||
+            ctx->events_used + 2 > ctx->events.size() || ctx->num_units == 0)
+            return;
+        t0 = ctx->events[ctx->events_used];
+        t1 = ctx->events[ctx->events_used + 1];
+    }
+    void launched(gd_ctx* ctx) const {
+        if (t0) ctx->events_used += 2;
+        if (ctx->num_units > 0) ++ctx->dense_launches;
+    }
+};
+
+// 1-bit quantisation of the sent list.  k_total is the host-known output size
+// (exact threshold), or under a sampled threshold the capacity, a bound the
+// device-side count stays within.
+gd_status run_quant(gd_ctx* ctx, float* residual, bool per, uint32_t ppm, bool direct, bool sampled, gd_quant quant,
+                    uint64_t k_total, const gd_sparse* out, hipStream_t st) {
+    if (quant == GD_QUANT_NONE) return GD_OK;
+    gd::QuantArgs qa{};
+    qa.res = residual;
+    qa.idx = out->idx;
+    qa.val = out->val;
+    qa.sign_bits = out->sign_bits;
+    qa.means = out->means;
+    qa.tensor_counts = out->tensor_counts;
+    qa.tile_base = ctx->scr.tile_base;
+    qa.ten_cbase = ctx->scr.ten_cbase;
+    qa.tile_q = ctx->scr.tile_q;
+    qa.qbase = ctx->scr.qbase;
+    qa.direct = direct ? 1u : 0u;
+    qa.tq = ctx->scr.tq;
+    qa.T = ctx->T;
+    qa.N = (uint32_t)ctx->N;
+    qa.k_total = k_total;
+    qa.qkind = (uint32_t)quant;
+    qa.per_tensor = per;
+    qa.keep_ppm = ppm;
+    qa.seg_off = per ? ctx->tab.tensor_off : ctx->tab.global_off;
+    qa.tensor_off = ctx->tab.tensor_off;
+    qa.seg = ctx->scr.seg;
+    qa.columns = ctx->cols.columns;
+    qa.colbase = ctx->cols.colbase;
+    qa.sampled = sampled ? 1u : 0u;
+    qa.groups = ctx->cols.groups;
+    qa.csum = ctx->cols.csum;
+    qa.ccnt = ctx->cols.ccnt;
+    return gd::launch_quant(qa, st) == hipSuccess ? GD_OK : GD_ERR_HIP;
+}
+
 // The passes after the threshold bracket is set: the dense stream, the
 // candidate layout, exact selection or plain compaction, and quantisation.
-// k_total is the host-known output size (exact threshold), or under a sampled
-// threshold the capacity, a bound the device-side count stays within.
 gd_status run_after_bracket(gd_ctx* ctx, const float* grad, const float* base, float* residual, bool per,
                             uint32_t ppm, bool sampled, gd_quant quant, uint64_t k_total, const gd_sparse* out,
                             hipStream_t st) {
@@ -133,13 +185,9 @@ gd_status run_after_bracket(gd_ctx* ctx, const float* grad, const float* base, f
     da.seg = ctx->scr.seg;
     da.slots = ctx->scr.slots;
     da.cnt = ctx->scr.cnt;
-    const bool timed = ctx->profile_every != 0 && ctx->dense_launches % ctx->profile_every == 0 &&
-                       ctx->events_used + 2 <= ctx->events.size() && ctx->num_units > 0;
-    hipEvent_t t0 = timed ? ctx->events[ctx->events_used] : nullptr;
-    hipEvent_t t1 = timed ? ctx->events[ctx->events_used + 1] : nullptr;
-    if (gd::launch_dense(da, base != nullptr, st, t0, t1) != hipSuccess) return GD_ERR_HIP;
-    if (timed) ctx->events_used += 2;
-    if (ctx->num_units > 0) ++ctx->dense_launches;
+    const DenseTimer timer(ctx);
+    if (gd::launch_dense(da, base != nullptr, st, timer.t0, timer.t1) != hipSuccess) return GD_ERR_HIP;
+    timer.launched(ctx);
 
     gd::CandArgs ca{};
     ca.res = residual;
@@ -190,57 +238,68 @@ gd_status run_after_bracket(gd_ctx* ctx, const float* grad, const float* base, f
     ea.val = out->val;
     ea.tensor_counts = out->tensor_counts;
     ea.capacity = out->capacity;
-    const bool q = quant != GD_QUANT_NONE;
     ea.qkind = (uint32_t)quant;
     if (gd::launch_layout(ca, st) != hipSuccess) return GD_ERR_HIP;
-    if (gd::launch_candidates(ca, ea, q, ctx->max_tiles, st) != hipSuccess) return GD_ERR_HIP;
-
-    if (q) {
-        gd::QuantArgs qa{};
-        qa.res = residual;
-        qa.idx = out->idx;
-        qa.val = out->val;
-        qa.sign_bits = out->sign_bits;
-        qa.means = out->means;
-        qa.tensor_counts = out->tensor_counts;
-        qa.tile_base = ctx->scr.tile_base;
-        qa.ten_cbase = ctx->scr.ten_cbase;
-        qa.tile_q = ctx->scr.tile_q;
-        qa.qbase = ctx->scr.qbase;
-        qa.T = ctx->T;
-        qa.N = (uint32_t)ctx->N;
-        qa.k_total = k_total;
-        qa.qkind = (uint32_t)quant;
-        qa.per_tensor = per;
-        qa.keep_ppm = ppm;
-        qa.seg_off = seg_off;
-        qa.tensor_off = ctx->tab.tensor_off;
-        qa.seg = ctx->scr.seg;
-        qa.columns = ctx->cols.columns;
-        qa.colbase = ctx->cols.colbase;
-        qa.sampled = sampled ? 1u : 0u;
-        qa.groups = ctx->cols.groups;
-        qa.csum = ctx->cols.csum;
-        qa.ccnt = ctx->cols.ccnt;
-        if (gd::launch_quant(qa, st) != hipSuccess) return GD_ERR_HIP;
-    }
-    return GD_OK;
+    if (gd::launch_candidates(ca, ea, quant != GD_QUANT_NONE, ctx->max_tiles, st) != hipSuccess) return GD_ERR_HIP;
+    return run_quant(ctx, residual, per, ppm, false, sampled, quant, k_total, out, st);
 }
 
 }  // namespace
 
 namespace gd {
 
+uint32_t direct_pieces(uint32_t C, uint32_t T) {
+    if (C > kDirectMaxUnits) return 0;
+    const uint32_t cu = direct_units_per_wave(C) * (kDirectThreads / kWave);
+    return (C + cu - 1) / cu + T;
+}
+
 gd_status compress_exact(gd_ctx* ctx, const float* grad, const float* base, float* residual, double drop_ratio,
                          bool per, gd_quant quant, uint64_t k_total, const gd_sparse* out, hipStream_t st) {
     const uint32_t ppm = (uint32_t)keep_ppm_of(drop_ratio);
+    const uint32_t* seg_off = per ? ctx->tab.tensor_off : ctx->tab.global_off;
+    const uint32_t S = per ? ctx->T : 1u;
+    if (ctx->num_units <= kDirectMaxUnits && ctx->debug_bracket == 0) {
+        DirectArgs a{};
+        a.grad = grad;
+        a.base = base;
+        a.res = residual;
+        if (!residual) {  // a pull from the last pulled copy (base)
+            a.pull_p = grad;
+            a.pull_copy = const_cast<float*>(base);
+        }
+        a.unit_info = ctx->tab.unit_info;
+        a.tensor_off = ctx->tab.tensor_off;
+        a.seg_off = seg_off;
+        a.N = (uint32_t)ctx->N;
+        a.C = ctx->num_units;
+        a.T = ctx->T;
+        a.S = S;
+        a.per_tensor = per;
+        a.keep_ppm = ppm;
+        a.seg = ctx->scr.seg;
+        a.h0 = ctx->scr.h0;
+        a.h1 = ctx->scr.h1;
+        a.copies = hist_copies(ctx->T);
+        a.info = ctx->scr.info;
+        a.ent = ctx->scr.cand_val;
+        a.out_base = ctx->scr.out_base;
+        a.tensor_counts = out->tensor_counts;
+        a.idx = out->idx;
+        a.val = out->val;
+        a.capacity = out->capacity;
+        const DenseTimer timer(ctx);
+        if (launch_direct(a, !residual ? 2 : base ? 1 : 0, st, timer.t0, timer.t1) != hipSuccess) return GD_ERR_HIP;
+        timer.launched(ctx);
+        return run_quant(ctx, residual, per, ppm, true, false, quant, k_total, out, st);
+    }
     SampleArgs sa{};
     sa.grad = grad;
     sa.base = base;
     sa.res = residual;
-    sa.seg_off = per ? ctx->tab.tensor_off : ctx->tab.global_off;
+    sa.seg_off = seg_off;
     sa.skey_base = per ? ctx->tab.skey_base_tensor : ctx->tab.skey_base_global;
-    sa.S = per ? ctx->T : 1u;
+    sa.S = S;
     sa.T = ctx->T;
     sa.keep_ppm = ppm;
     sa.debug_bracket = ctx->debug_bracket;
@@ -359,6 +418,11 @@ gd_status gd_create(gd_ctx** out, const uint64_t* off, uint32_t T) {
          dev_alloc(ctx, &ctx->scr.skeys, std::max(ctx->skeys_tensor, ctx->skeys_global)) &&
          dev_alloc(ctx, &ctx->scr.qbase, T + 1) && dev_alloc(ctx, &ctx->scr.shist, (size_t)S_max * gd::kSHistWords) &&
          dev_alloc(ctx, &ctx->scr.sshist, (size_t)S_max * gd::kSsCopies * gd::kSsNB0);
+    const bool direct = C <= gd::kDirectMaxUnits;  // larger layouts never take the direct form
+    const size_t h_words = direct ? (size_t)S_max * gd::hist_copies(T) * gd::kSelBins : 0;
+    ok = ok && dev_alloc(ctx, &ctx->scr.tq, direct ? 4 * (size_t)(N / gd::kQSlice + 1 + T) : 0) &&
+         dev_alloc(ctx, &ctx->scr.info, gd::direct_pieces(C, T)) && dev_alloc(ctx, &ctx->scr.h0, h_words) &&
+         dev_alloc(ctx, &ctx->scr.h1, h_words);
     if (!ok) {
         free_all(ctx);
         delete ctx;
@@ -370,6 +434,7 @@ gd_status gd_create(gd_ctx** out, const uint64_t* off, uint32_t T) {
         return GD_ERR_OOM;
     }
     if (hipMemset(ctx->scr.seg, 0, S_max * sizeof(gd::SegState)) != hipSuccess ||
+        (h_words && hipMemset(ctx->scr.h0, 0, h_words * sizeof(uint32_t)) != hipSuccess) ||
         hipMemset(ctx->scr.shist, 0, (size_t)S_max * gd::kSHistWords * sizeof(uint32_t)) != hipSuccess ||
         hipMemset(ctx->scr.sshist, 0, (size_t)S_max * gd::kSsCopies * gd::kSsNB0 * sizeof(uint32_t)) != hipSuccess ||
         hipMemset(ctx->scr.ten_cbase, 0, (T + 1) * sizeof(uint32_t)) != hipSuccess ||
@@ -419,27 +484,8 @@ gd_status gd_compress_pull(gd_ctx* ctx, const float* params, float* copy, double
 
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return GD_ERR_HIP;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool per = mode == GD_PER_TENSOR;
-    const uint32_t ppm = (uint32_t)keep_ppm_of(drop_ratio);
-    gd::SampleArgs sa{};
-    sa.grad = params;
-    sa.base = copy;
-    sa.res = nullptr;  // acc = params - copy
-    sa.seg_off = per ? ctx->tab.tensor_off : ctx->tab.global_off;
-    sa.skey_base = per ? ctx->tab.skey_base_tensor : ctx->tab.skey_base_global;
-    sa.S = per ? ctx->T : 1u;
-    sa.T = ctx->T;
-    sa.keep_ppm = ppm;
-    sa.debug_bracket = ctx->debug_bracket;
-    sa.skeys = ctx->scr.skeys;
-    sa.seg = ctx->scr.seg;
-    sa.hist = ctx->scr.hist;
-    sa.shist = ctx->scr.shist;
-    sa.out_base = ctx->scr.out_base;
-    sa.tensor_counts = out->tensor_counts;
-    if (gd::launch_sample(sa, true, st) != hipSuccess) return GD_ERR_HIP;
-    return run_after_bracket(ctx, params, copy, nullptr, per, ppm, false, GD_QUANT_NONE, k_total, out, st);
+    return gd::compress_exact(ctx, params, copy, nullptr, drop_ratio, mode == GD_PER_TENSOR, GD_QUANT_NONE, k_total, out,
+                              static_cast<hipStream_t>(stream));
 }
 
 gd_status gd_set_columns(gd_ctx* ctx, const uint32_t* columns) {

@@ -94,7 +94,7 @@ struct SegState {
     uint32_t hi;    // the dense pass wrote residual = +0 where key >= hi
     uint32_t clo;   // number of candidates (key >= lo)
     uint32_t miss;  // 1 when fewer than k candidates: every element becomes one
-    uint32_t d0;    // digit 0 of the threshold key (key >> 21)
+    uint32_t d0;    // digit 0 of the threshold key (key >> 21; direct form: key >> 20)
     uint32_t r1;    // rank of the threshold among candidates with that digit 0
     uint32_t p18;   // key >> 13 of the threshold key
     uint32_t r2;    // rank among candidates with that prefix
@@ -103,7 +103,9 @@ struct SegState {
     uint32_t zero;  // 1 when fewer than k keys are nonzero and all of them are candidates: T = 0
     uint32_t runs;  // kept between calls: 1 when the last sample's units counted like independent
                     // draws, so the next call samples one run of 16 neighbours per unit
-    uint32_t pad[4];
+    uint32_t blo;   // direct form: the keys [blo, blo + 2^bbits) that hold the threshold key
+    uint32_t bbits;
+    uint32_t pad[2];
 };
 
 __device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }

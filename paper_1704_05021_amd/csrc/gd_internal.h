@@ -8,6 +8,7 @@
 
 #include "gd.h"
 #include "gd_device.hpp"
+#include "gd_kernels.h"
 
 namespace gd {
 
@@ -55,6 +56,10 @@ struct Scratch {
     uint16_t* skeys = nullptr;       // 16-bit sample keys
     uint32_t* shist = nullptr;       // [S_max * kSHistWords] sample histograms, kept zero between calls
     uint32_t* qbase = nullptr;       // [T + 1] first output slot of each tensor
+    PieceInfo* info = nullptr;       // direct form: [pieces]
+    uint32_t* h0 = nullptr;          // [S_max * copies * kSelBins] its first digit; clear between calls
+    uint32_t* h1 = nullptr;          // [S_max * copies * kSelBins] its second digit
+    double* tq = nullptr;            // [(N / kQSlice + 1 + T) * 4] its quantisation sums
     uint32_t* sshist = nullptr;      // [S_max * kSsCopies * kSsNB0] sampled mode: top-digit histograms
 };
 
@@ -73,9 +78,21 @@ struct gd_ctx;
 
 namespace gd {
 
-// The launch sequence of one exact-threshold compression (sample, bracket,
-// dense pass, candidate passes, quantisation) on the tables and scratch ctx
-// points to, after the caller's argument checks; k_total is the output size.
+// Gradients of at most this many units take the direct form (gd_direct.hip):
+// its passes grow with the elements, the candidate form's mostly do not.  One
+// threshold over an MLP, direct against candidate form, us a call: 31 against
+// 60 at 2.1M elements, 42 against 66 at 4.2M, 51 against 69 at 6.1M, 76
+// against 74 at 8.8M.
+constexpr uint32_t kDirectMaxUnits = 6144;
+// Records the direct form keeps for C units and T tensors (none past the limit).
+uint32_t direct_pieces(uint32_t C, uint32_t T);
+// Copies of each segment's histograms in a layout of T tensors.
+inline uint32_t hist_copies(uint32_t T) { return T <= kCopiesMaxT ? (uint32_t)kHistCopies : 1u; }
+
+// The launch sequence of one exact-threshold compression (the direct form, or
+// sample, bracket, dense pass and candidate passes; then quantisation) on the
+// tables and scratch ctx points to, after the caller's argument checks;
+// k_total is the output size.  A null residual is a pull from the copy, base.
 gd_status compress_exact(gd_ctx* ctx, const float* grad, const float* base, float* residual, double drop_ratio,
                          bool per, gd_quant quant, uint64_t k_total, const gd_sparse* out, hipStream_t st);
 

@@ -120,6 +120,53 @@ struct CandArgs {
     float* pull_copy;     //   and the copy, which takes the sent values
 };
 
+// The direct form of the exact selection (gd_direct.hip): histograms of
+// kSelBins bins resolve the 31 key bits from the top, 11, 11 and 9 at a time.
+constexpr int kSelBins = 2048;
+constexpr int kSel0Shift = 20;
+// Every histogram is kept in copies, picked by block number modulo their
+// number, which the next pass sums.  Blocks go to the eight XCDs in turn, so
+// each copy's lines stay in one XCD's L2: adds from several XCDs to one line
+// move it between their caches, about 40 to 200 ns each.  Layouts of more
+// than kCopiesMaxT tensors keep one copy (their segments are small).
+constexpr int kHistCopies = 8;
+constexpr uint32_t kCopiesMaxT = 1024;
+
+constexpr int kDirectThreads = 256;    // block of the direct form
+
+// What a pass leaves about one piece (one threshold segment in one chunk).
+struct PieceInfo {
+    uint32_t gt;    // keys above the bin
+    uint32_t in;    // keys inside it
+    uint32_t kmin;  // the smallest and largest of those
+    uint32_t kmax;
+};
+
+struct DirectArgs {
+    const float* grad;   // the inputs of the first pass
+    const float* base;
+    float* res;          // holds acc after the first pass; null for a pull from the copy:
+    const float* pull_p;   // the parameters
+    float* pull_copy;      // and the copy, which takes the sent values
+    const uint32_t* unit_info;   // [C] tensor of the unit's first element | (holds a tensor start) << 31
+    const uint32_t* tensor_off;  // [T + 1]
+    const uint32_t* seg_off;     // [S + 1]
+    uint32_t N, C, T, S;         // elements, units, tensors, threshold segments
+    uint32_t per_tensor;
+    uint32_t keep_ppm;
+    uint32_t cshift, G;          // log2 of a chunk's elements, chunks (set by the launcher)
+    SegState* seg;               // [S]
+    uint32_t *h0, *h1;           // [S * copies * kSelBins]; h0 is clear between calls
+    uint32_t copies;
+    PieceInfo* info;             // [pieces]
+    uint32_t* ent;               // [N] the bin's keys of the piece that starts at element e, from ent[e]
+    uint64_t* out_base;          // [S] first output slot of each segment
+    uint32_t* tensor_counts;
+    uint32_t* idx;
+    float* val;
+    uint64_t capacity;
+};
+
 // 1-bit centres (Section 5.4): per-tensor sign means, the dropping threshold,
 // one global average, or column-wise averages.
 constexpr uint32_t kQuantSignMean = 1, kQuantThreshold = 2, kQuantGlobalMean = 3, kQuantColumnMean = 4;
@@ -158,7 +205,11 @@ struct QuantArgs {
     uint32_t groups;            // column groups (column-wise centres)
     double* csum;               // [2 * groups] column sums (positive, negative), zero on entry, cleared after use
     uint32_t* ccnt;             // [2 * groups] column counts, likewise
+    uint32_t direct;            // after the direct form, which keeps no tile sums:
+    double* tq;                 // [slices * 4 + 4 T] sums and counts of the sent entries, per slice and tensor
 };
+
+constexpr uint32_t kQSlice = 4096;  // sent entries per partial sum after the direct form
 
 constexpr uint32_t kMaxPushes = 64;
 
@@ -191,6 +242,9 @@ hipError_t launch_layout(const CandArgs& a, hipStream_t st);
 hipError_t launch_dense(const DenseArgs& a, bool has_base, hipStream_t st, hipEvent_t t0 = nullptr,
                         hipEvent_t t1 = nullptr);
 hipError_t launch_candidates(const CandArgs& a, const EmitArgs& o, bool quant, uint32_t max_tiles, hipStream_t st);
+// The direct form; t0, t1: as launch_dense, for its first pass.
+hipError_t launch_direct(DirectArgs a, int mode, hipStream_t st, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+uint32_t direct_units_per_wave(uint32_t units);
 hipError_t launch_quant(const QuantArgs& q, hipStream_t st);
 hipError_t launch_apply(const ApplyArgs& a, uint32_t max_nnz, hipStream_t st);
 // Form of later applies: 0 chosen per call, 1 scattered, 2 streaming wherever the parameters are 16-byte aligned.

@@ -97,6 +97,152 @@ __global__ __launch_bounds__(kBlock) void k_means(QuantArgs q) {
     }
 }
 
+// After the direct form (exact thresholds only, no tile sums): the sums come
+// from the sent list itself.
+//
+// The first output slot of each tensor, where one block cannot do it on the
+// way (more than kMeansThreads tensors).
+constexpr int kMeansThreads = 1024;
+constexpr uint32_t kMeansLocalT = kMeansThreads - 1;
+// Sent entries that one block per tensor sums directly; more are summed per
+// slice first.  One block of 1,024 threads takes about 0.1 us per 1,024 entries.
+constexpr uint32_t kMeansDirectK = 65536;
+
+__global__ __launch_bounds__(kMeansThreads) void k_qbase(QuantArgs q) {
+    __shared__ uint32_t lds[kMeansThreads / kWave + 1];
+    uint32_t carry = 0;
+    for (uint32_t t0 = 0; t0 < q.T; t0 += kMeansThreads) {
+        const uint32_t t = t0 + threadIdx.x;
+        uint32_t total;
+        const uint32_t excl = block_excl_scan<kMeansThreads>(t < q.T ? q.tensor_counts[t] : 0u, lds, &total);
+        if (t < q.T) q.qbase[t] = carry + excl;
+        carry += total;
+    }
+    if (threadIdx.x == 0) q.qbase[q.T] = carry;
+}
+
+// Sums of four doubles over a block of NT threads, in every thread.
+template <int NT>
+__device__ __forceinline__ void block_sum4(double v[4], double* lds) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = wave_sum(v[i]);
+    if (lane_id() == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lds[4 * (threadIdx.x / kWave) + i] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = lds[i];
+        for (int w = 1; w < NT / kWave; ++w) v[i] += lds[4 * w + i];
+    }
+    __syncthreads();
+}
+
+// One more sent value into the sums and counts (positive sum, negative sum,
+// positive count, negative count).
+__device__ __forceinline__ void add_value(double v[4], float x) {
+    if (x < 0.0f) {
+        v[1] += (double)x;
+        v[3] += 1.0;
+    } else {
+        v[0] += (double)x;
+        v[2] += 1.0;
+    }
+}
+
+// Sums of every slice of kQSlice sent entries: per tensor under the sign mean
+// (slice j and tensor t have record j + t: along the list either grows from
+// one pair to the next, so a tensor's records are consecutive), else over all.
+__global__ __launch_bounds__(kBlock) void k_qsum(QuantArgs q) {
+    __shared__ double lds[4 * kWavesPerBlock];
+    const int tid = threadIdx.x;
+    constexpr int PER = kQSlice / kBlock;
+    const uint64_t j0 = (uint64_t)blockIdx.x * kQSlice, j1 = j0 + kQSlice < q.k_total ? j0 + kQSlice : q.k_total;
+    const bool own = q.qkind == kQuantSignMean;
+    uint32_t t = 0;
+    float x[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint64_t j = j0 + i * kBlock + tid;
+        x[i] = j < j1 ? q.val[j] : 0.0f;
+    }
+    if (own) {  // tensor of slot j0: the last t with qbase[t] <= j0
+        uint32_t hi = q.T;
+        while (hi - t > 1) {
+            const uint32_t mid = (t + hi) >> 1;
+            if (q.qbase[mid] <= j0) t = mid;
+            else hi = mid;
+        }
+    }
+    for (uint64_t j = j0; j < j1;) {  // block-uniform walk over the tensors of the slice
+        while (own && q.qbase[t + 1] <= j) ++t;
+        const uint64_t e = own && q.qbase[t + 1] < j1 ? q.qbase[t + 1] : j1;
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t at = j0 + i * kBlock + tid;
+            if (at >= j && at < e) add_value(v, x[i]);
+        }
+        block_sum4<kBlock>(v, lds);
+        if (tid == 0)
+            for (int i = 0; i < 4; ++i) q.tq[4 * ((size_t)blockIdx.x + t) + i] = v[i];
+        j = e;
+    }
+}
+
+// Centres per tensor (every kind but the column mean) and the first output
+// slot of each tensor.  One block per tensor.
+__global__ __launch_bounds__(kMeansThreads) void k_dmeans(QuantArgs q, uint32_t sliced, uint32_t have_base) {
+    constexpr int NT = kMeansThreads, U = 8;
+    __shared__ double lds[4 * (NT / kWave)];
+    __shared__ uint32_t first[NT + 1], scan[NT / kWave + 1];
+    const int tid = threadIdx.x;
+    const uint32_t t = blockIdx.x;
+    const uint32_t* qbase = q.qbase;
+    if (!have_base) {
+        uint32_t total;
+        const uint32_t excl = block_excl_scan<NT>((uint32_t)tid < q.T ? q.tensor_counts[tid] : 0u, scan, &total);
+        first[tid] = excl;
+        if (t == 0 && (uint32_t)tid <= q.T) q.qbase[tid] = excl;
+        __syncthreads();
+        qbase = first;
+    }
+    if (q.qkind == kQuantColumnMean) return;
+    float pos = 0.0f, neg = 0.0f;
+    if (q.qkind == kQuantThreshold) {
+        // the smallest kept magnitude of the segment is the exact threshold key
+        const uint32_t s = q.per_tensor ? t : 0u;
+        if (keep_of(q.seg_off[s + 1] - q.seg_off[s], q.keep_ppm) > 0) {
+            pos = __uint_as_float(q.seg[s].thr);
+            neg = __uint_as_float(q.seg[s].thr | 0x80000000u);
+        }
+    } else {
+        const bool own = q.qkind == kQuantSignMean;
+        const uint32_t a = own ? qbase[t] : 0u, b = own ? qbase[t + 1] : qbase[q.T];
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        if (sliced) {
+            for (uint32_t r = a / kQSlice + tid; a < b && r <= (b - 1) / kQSlice; r += NT)
+                for (int i = 0; i < 4; ++i) v[i] += q.tq[4 * ((size_t)r + (own ? t : 0u)) + i];
+        } else {
+            for (uint32_t j = a + tid; j < b; j += U * NT) {
+                float x[U];
+#pragma unroll
+                for (int i = 0; i < U; ++i) x[i] = b - j > (uint32_t)i * NT ? q.val[j + i * NT] : 0.0f;
+#pragma unroll
+                for (int i = 0; i < U; ++i)
+                    if (b - j > (uint32_t)i * NT) add_value(v, x[i]);
+            }
+        }
+        block_sum4<NT>(v, lds);
+        pos = v[2] > 0.0 ? (float)(v[0] / v[2]) : 0.0f;
+        neg = v[3] > 0.0 ? (float)(v[1] / v[3]) : 0.0f;
+    }
+    if (tid == 0) {
+        q.means[2 * t + 0] = pos;
+        q.means[2 * t + 1] = neg;
+    }
+}
+
 // Column sums of the sent entries, per sign.  Each block takes a slice of
 // kColSlice consecutive output slots and walks the tensors it touches; for a
 // tensor of at most kColLds columns it sums the slice in LDS first (fp64 LDS
@@ -198,7 +344,17 @@ __global__ __launch_bounds__(kBlock) void k_quant(QuantArgs q) {
 static inline uint32_t blocks_for_waves(uint32_t waves) { return (waves + kWavesPerBlock - 1) / kWavesPerBlock; }
 
 hipError_t launch_quant(const QuantArgs& q, hipStream_t st) {
-    hipLaunchKernelGGL(k_means, dim3(blocks_for_waves(q.T)), dim3(kBlock), 0, st, q);
+    if (q.direct) {
+        const bool sums = q.qkind == kQuantSignMean || q.qkind == kQuantGlobalMean;
+        const bool sliced = sums && q.k_total > kMeansDirectK, base = sliced || q.T > kMeansLocalT;
+        if (base) hipLaunchKernelGGL(k_qbase, dim3(1), dim3(kMeansThreads), 0, st, q);
+        if (sliced) hipLaunchKernelGGL(k_qsum, dim3((uint32_t)((q.k_total + kQSlice - 1) / kQSlice)), dim3(kBlock), 0, st, q);
+        // (column means need the first slots only, of one block)
+        hipLaunchKernelGGL(k_dmeans, dim3(q.qkind == kQuantColumnMean ? 1u : q.T), dim3(kMeansThreads), 0, st, q,
+                           sliced ? 1u : 0u, base ? 1u : 0u);
+    } else {
+        hipLaunchKernelGGL(k_means, dim3(blocks_for_waves(q.T)), dim3(kBlock), 0, st, q);
+    }
     if (q.qkind == kQuantColumnMean && q.groups > 0) {
         if (q.k_total > 0)
             hipLaunchKernelGGL(k_colsum, dim3((uint32_t)((q.k_total + kColSlice - 1) / kColSlice)), dim3(kBlock), 0, st,

@@ -12,6 +12,7 @@
 // earlier call, of any layout.  Nothing is allocated: no hipMalloc, no host
 // heap, no memset node.
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -24,8 +25,9 @@ namespace gd {
 
 constexpr uint64_t kStaticMaxN = 1ull << 21;  // elements of the layout (2,097,152)
 constexpr uint32_t kStaticMaxT = 64;          // tensors of the layout
-constexpr size_t kStaticBytes = 48ull << 20;  // the scratch array: 48 MiB per GPU
+constexpr size_t kStaticBytes = 24ull << 20;  // the scratch array: 24 MiB per GPU
 constexpr int kStaticMaxDevices = 64;
+static_assert(kStaticMaxN <= (uint64_t)kDirectMaxUnits * kUnitLen, "only the direct form's scratch is laid out here");
 
 // Every gd_compress_static call on a device shares that device's copy.
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
@@ -64,56 +66,23 @@ struct Carver {
     }
 };
 
-// Sample keys stored for a segment [a, b): 16 per sample unit.
-uint32_t sample_keys(uint64_t a, uint64_t b) {
-    if (b <= a) return 0;
-    const uint64_t n16 = ((b - 1) >> 4) - (a >> 4) + 1;
-    return (uint32_t)kUnit * sample_unit_count((uint32_t)n16);
-}
-
 // Points ctx's tables and scratch into the array at base; returns the bytes
-// used.  The sizes follow gd_create's for the same layout, except that the
-// sampled mode's histograms and the column tables are left out.
+// used.  The sizes follow gd_create's for the same layout; what only the
+// candidate form, the sampled mode or the column-wise centres use is left out.
 size_t carve(gd_ctx& ctx, unsigned char* base) {
     Carver c{base};
-    const uint32_t C = ctx.num_units, T = ctx.T, MT = ctx.max_tiles;
-    const uint32_t sb = (C + kScanUnits - 1) / kScanUnits;
+    const uint32_t C = ctx.num_units, T = ctx.T;
     ctx.tab.unit_info = c.take<uint32_t>(C);
     ctx.tab.tensor_off = c.take<uint32_t>(T + 1);
     ctx.tab.global_off = c.take<uint32_t>(2);
-    ctx.tab.skey_base_tensor = c.take<uint32_t>(T + 1);
-    ctx.tab.skey_base_global = c.take<uint32_t>(2);
-    ctx.scr.slots = c.take<uint2>((size_t)C * kUnitLen);
-    ctx.scr.cnt = c.take<uint32_t>(C);
-    ctx.scr.split = c.take<uint32_t>(T);
-    ctx.scr.loc = c.take<uint32_t>(C);
-    ctx.scr.neloc = c.take<uint32_t>(C);
-    ctx.scr.btot = c.take<uint32_t>(sb);
-    ctx.scr.betot = c.take<uint32_t>(sb);
-    ctx.scr.boff = c.take<uint32_t>(sb);
-    ctx.scr.beoff = c.take<uint32_t>(sb);
-    ctx.scr.ne_unit = c.take<uint32_t>(C);
-    ctx.scr.ne_off = c.take<uint32_t>((size_t)C + 1);
-    ctx.scr.num_ne = c.take<uint32_t>(1);
-    ctx.scr.raw_tbase = c.take<uint32_t>(T + 1);
-    ctx.scr.cand_idx = c.take<uint32_t>(ctx.N);
+    ctx.scr.info = c.take<PieceInfo>(direct_pieces(C, T));
     ctx.scr.cand_val = c.take<uint32_t>(ctx.N);
-    ctx.scr.ten_cbase = c.take<uint32_t>(T + 1);
-    ctx.scr.tile_base = c.take<uint32_t>(T + 1);
-    ctx.scr.tile_desc = c.take<uint32_t>((size_t)MT * kTileDescWords);
-    ctx.scr.tile_gt = c.take<uint32_t>(MT);
-    ctx.scr.tile_eq = c.take<uint32_t>(MT);
-    ctx.scr.grp_gt = c.take<uint32_t>(MT / kGroupTiles + 1);
-    ctx.scr.grp_eq = c.take<uint32_t>(MT / kGroupTiles + 1);
-    ctx.scr.tile_q = c.take<double>(4 * (size_t)MT);
-    ctx.scr.flags = c.take<uint32_t>(4);
-    ctx.scr.hist = c.take<uint32_t>((size_t)T * kHistWords);
+    ctx.scr.h0 = c.take<uint32_t>((size_t)T * hist_copies(T) * kSelBins);
+    ctx.scr.h1 = c.take<uint32_t>((size_t)T * hist_copies(T) * kSelBins);
+    ctx.scr.tq = c.take<double>(4 * (size_t)(ctx.N / kQSlice + 1 + T));
     ctx.scr.seg = c.take<SegState>(T);
     ctx.scr.out_base = c.take<uint64_t>(T);
-    ctx.scr.skeys = c.take<uint16_t>(ctx.skeys_tensor > ctx.skeys_global ? ctx.skeys_tensor : ctx.skeys_global);
     ctx.scr.qbase = c.take<uint32_t>(T + 1);
-    ctx.scr.shist = c.take<uint32_t>((size_t)T * kSHistWords);
-    ctx.scr.sshist = nullptr;
     return c.used;
 }
 
@@ -123,23 +92,12 @@ struct SetupArgs {
     uint32_t* unit_info;
     uint32_t* tensor_off;
     uint32_t* global_off;
-    uint32_t* skey_base_tensor;
-    uint32_t* skey_base_global;
-    uint32_t* seg_words;  // T * 16 words of SegState
-    uint32_t* shist;      // T * kSHistWords
-    uint32_t* ten_cbase;
-    uint32_t* tile_base;
-    uint32_t* qbase;
+    uint32_t* h0;         // histogram words to clear
+    uint32_t h0_words;
 };
 
-__device__ __forceinline__ uint32_t sample_keys_dev(uint32_t a, uint32_t b) {
-    if (b <= a) return 0;
-    return (uint32_t)kUnit * sample_unit_count(((b - 1) >> 4) - (a >> 4) + 1);
-}
-
-// The layout tables gd_create would upload, and the state that starts at
-// zero.  One thread per unit or cleared word; thread 0 also scans the
-// sample-key bases (at most 64 tensors).
+// The layout tables gd_create would upload, and the histograms that start at
+// zero.  One thread per unit or cleared word.
 __global__ __launch_bounds__(kBlock) void k_static_setup(SetupArgs a) {
     const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
     if (g < a.C) {
@@ -152,25 +110,9 @@ __global__ __launch_bounds__(kBlock) void k_static_setup(SetupArgs a) {
         for (uint32_t x = t + 1; x < a.T && a.off[x] < ue; ++x) inside = inside || a.off[x] > us;
         a.unit_info[g] = t | (inside ? 0x80000000u : 0u);
     }
-    if (g <= a.T) {
-        a.tensor_off[g] = a.off[g];
-        a.ten_cbase[g] = 0;
-        a.tile_base[g] = 0;
-        a.qbase[g] = 0;
-    }
+    if (g <= a.T) a.tensor_off[g] = a.off[g];
     if (g < 2) a.global_off[g] = g ? a.N : 0u;
-    if (g < a.T * (uint32_t)(sizeof(SegState) / 4)) a.seg_words[g] = 0;
-    if (g < a.T * (uint32_t)kSHistWords) a.shist[g] = 0;
-    if (g == 0) {
-        uint32_t acc = 0;
-        for (uint32_t t = 0; t < a.T; ++t) {
-            a.skey_base_tensor[t] = acc;
-            acc += sample_keys_dev(a.off[t], a.off[t + 1]);
-        }
-        a.skey_base_tensor[a.T] = acc;
-        a.skey_base_global[0] = 0;
-        a.skey_base_global[1] = sample_keys_dev(0, a.N);
-    }
+    if (g < a.h0_words) a.h0[g] = 0;
 }
 
 uint64_t keep_of_host(uint64_t n, double drop_ratio) {
@@ -220,15 +162,6 @@ extern "C" gd_status gd_compress_static(const uint64_t* off, uint32_t T, const f
     ctx.T = T;
     ctx.N = N;
     ctx.num_units = (uint32_t)((N + kUnitLen - 1) / kUnitLen);
-    uint64_t tiles = 0;
-    uint32_t sk = 0;
-    for (uint32_t t = 0; t < T; ++t) {
-        tiles += (off[t + 1] - off[t] + kTile - 1) / kTile;
-        sk += sample_keys(off[t], off[t + 1]);
-    }
-    ctx.max_tiles = (uint32_t)tiles;
-    ctx.skeys_tensor = sk;
-    ctx.skeys_global = sample_keys(0, N);
     if (carve(ctx, nullptr) > kStaticBytes) return GD_ERR_LAYOUT;  // cannot happen within the limits above
 
     if (hipGetDevice(&ctx.device) != hipSuccess) return GD_ERR_HIP;
@@ -244,15 +177,9 @@ extern "C" gd_status gd_compress_static(const uint64_t* off, uint32_t T, const f
     sa.unit_info = ctx.tab.unit_info;
     sa.tensor_off = ctx.tab.tensor_off;
     sa.global_off = ctx.tab.global_off;
-    sa.skey_base_tensor = ctx.tab.skey_base_tensor;
-    sa.skey_base_global = ctx.tab.skey_base_global;
-    sa.seg_words = reinterpret_cast<uint32_t*>(ctx.scr.seg);
-    sa.shist = ctx.scr.shist;
-    sa.ten_cbase = ctx.scr.ten_cbase;
-    sa.tile_base = ctx.scr.tile_base;
-    sa.qbase = ctx.scr.qbase;
-    uint32_t work = sa.C;
-    if (T * (uint32_t)kSHistWords > work) work = T * (uint32_t)kSHistWords;
+    sa.h0 = ctx.scr.h0;
+    sa.h0_words = (per ? T : 1u) * hist_copies(T) * (uint32_t)kSelBins;
+    uint32_t work = std::max(std::max(sa.C, T + 1), std::max(sa.h0_words, 2u));
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k_static_setup, dim3((work + kBlock - 1) / kBlock), dim3(kBlock), 0, st, sa);
     if (hipGetLastError() != hipSuccess) return GD_ERR_HIP;

@@ -1,0 +1,80 @@
+"""The direct form of the exact compressor (every element read in every pass,
+taken by gradients of at most 6,291,456 elements) against the oracle, at the
+sizes and values where its pieces, records and rules change: chunk and vector
+edges, more than 64 and more than 1,024 tensors, many keys inside one 22-bit
+prefix (equal, different, in pieces that store counts in place of keys),
+1-bit sums taken by slices, and a context that alternates with the candidate
+form."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1704_05021_amd import gd
+from parity import check_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _layout(rng, n, tensors):
+    return [0] + np.sort(rng.integers(0, n + 1, tensors - 1)).tolist() + [n]
+
+
+@pytest.mark.parametrize("tensors", [1, 5, 64, 65, 1025])
+@pytest.mark.parametrize("n", [1, 3, 1023, 4096, 4097, 16_387, 1_000_003, 4_718_592, 4_718_593, 6_291_456])
+def test_sizes(n, tensors):
+    rng = np.random.default_rng(n + tensors)
+    off = _layout(rng, n, tensors)
+    g = (rng.standard_t(3, n) * 1e-3).astype(np.float32)
+    r = (rng.normal(0, 1e-3, n) * (rng.random(n) < 0.5)).astype(np.float32)
+    comp = gd.Compressor(off)
+    for per, quant, drop in ((False, gd.GD_QUANT_SIGN_MEAN, 0.99), (True, False, 0.9))[:2 if n < 4_000_000 else 1]:
+        check_case(g, r, off, drop, per, quant, comp=comp, what=f"n={n} T={tensors} per={per}")
+
+
+@pytest.mark.parametrize("spread", [1, 2, 40, 512, 3000], ids=lambda s: f"{s}_values")
+@pytest.mark.parametrize("per_tensor", [False, True], ids=["global", "per_tensor"])
+def test_many_keys_in_one_prefix(per_tensor, spread):
+    # `spread` neighbouring binary32 values share the threshold's prefix (512 low
+    # bits), far more of them than one piece stores as keys; both forms in turn
+    rng = np.random.default_rng(spread)
+    n = 60_000
+    off = [0, 7, 30_001, n]
+    g = (np.float32(1.0).view(np.uint32) + rng.integers(0, spread, n).astype(np.uint32)).view(np.float32)
+    g = g * np.where(rng.random(n) < 0.5, -1, 1).astype(np.float32)
+    g[rng.random(n) < 0.02] *= 4.0
+    comp = gd.Compressor(off)
+    for drop in (0.99, 0.5):
+        for debug in (0, 3, 0):
+            check_case(g, np.zeros(n, np.float32), off, drop, per_tensor, gd.GD_QUANT_THRESHOLD, comp=comp,
+                       debug_bracket=debug, what=f"spread={spread} drop={drop} debug={debug}")
+
+
+@pytest.mark.parametrize("quant", [gd.GD_QUANT_SIGN_MEAN, gd.GD_QUANT_GLOBAL_MEAN], ids=["sign_mean", "global_mean"])
+@pytest.mark.parametrize("keep", [65_536, 65_537])
+def test_sums_by_slices(quant, keep):
+    rng = np.random.default_rng(keep)
+    n = 400_000
+    off = [0, 100, 100, 300_000, n]
+    g = rng.normal(0, 1e-3, n).astype(np.float32)
+    check_case(g, np.zeros(n, np.float32), off, 1.0 - keep / n, False, quant, what=f"keep={keep}")
+    assert gd.keep_count(n, 1.0 - keep / n) in (keep, keep - 1)
+
+
+@pytest.mark.parametrize("n", [5, 4_098, 300_003])
+def test_pull_from_copy(n):
+    rng = np.random.default_rng(n)
+    p = rng.normal(0, 1e-2, n).astype(np.float32)
+    copy = np.where(rng.random(n) < 0.9, p, p + rng.normal(0, 1e-3, n)).astype(np.float32)
+    off = _layout(rng, n, 3)
+    comp = gd.Compressor(off)
+    for per in (False, True):
+        for drop in (0.99, 0.5):  # the second keeps zeros
+            pt, ct = torch.from_numpy(p).cuda(), torch.from_numpy(copy).cuda()
+            out = comp.compress_pull(pt, ct, drop, per_tensor=per)
+            torch.cuda.synchronize()
+            o, oc = oracle.compress_pull(p, copy, off, drop, per_tensor=per)
+            assert np.array_equal(out.idx[:out.k].cpu().numpy().view(np.uint32), o.idx)
+            assert np.array_equal(out.val[:out.k].cpu().numpy().view(np.uint32), o.val.view(np.uint32))
+            assert np.array_equal(ct.cpu().numpy().view(np.uint32), oc.view(np.uint32))
+            assert np.array_equal(out.tensor_counts[:comp.T].cpu().numpy().view(np.uint32), o.tensor_counts)
