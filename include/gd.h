@@ -236,9 +236,9 @@ gd_status gd_compress_sampled(gd_ctx* ctx, const float* grad, const float* base,
  *   stream (per host thread for the per-thread default stream) and reuses it
  *   on later calls on that stream; it is allocated with hipMalloc on the
  *   first call that needs it (or a larger one) and kept until the process
- *   ends, so make the first call on a stream outside graph capture.  If that
- *   allocation fails the pushes are applied in the other form; the results
- *   are the same.
+ *   ends, so make the first call on a stream outside graph capture (a captured
+ *   call of more than 8 pushes needs no table).  If that allocation fails the
+ *   pushes are applied in the other form; the results are the same.
  *   The result is deterministic when the precondition above holds.  It is not
  *   checked on the device (that would need a host synchronisation): an index
  *   repeated inside one push is applied by two threads that race, and an
@@ -334,9 +334,10 @@ gd_status gd_debug_force_bracket(gd_ctx* ctx, int mode);
  * in this process, so that tests can run both forms at any density.  The
  * results do not change; only the work done does.  form 0: chosen per call
  * (streaming, which reads the whole shard in order, when params is 16-byte
- * aligned, the pushes hold at least one entry per 64 parameters, and there
- * are at most 8 of them; else scattered, which reads only the pushed
- * parameters); 1: scattered; 2: streaming wherever params is 16-byte
+ * aligned and the pushes hold at least one entry per 24 to 128 parameters, by
+ * the size of the shard and the number of pushes, and the call is not a
+ * captured one of more than 8 pushes; else scattered, which reads only the
+ * pushed parameters); 1: scattered; 2: streaming wherever params is 16-byte
  * aligned.  A process-wide setting: it applies to every device and thread.
  * GD_ERR_ARG for other forms.
  */

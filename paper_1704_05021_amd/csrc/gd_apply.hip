@@ -12,11 +12,11 @@
 // Quantised pushes (indices, sign bits, centre pairs; Section 5.4) are decoded
 // entry by entry where their values are read.
 //
-// The scattered form: one block per bucket of 2^15 consecutive parameter
-// indices.  The block finds where the bucket starts and ends in every
-// client's (ascending) index list by a 32-way search per half-wave (four
-// rounds of loads for a list of a few hundred thousand entries, instead of a
-// binary search's twenty), stages those entries in LDS, marking the indices
+// The scattered form: one block per bucket of 2^11 to 2^15 consecutive parameter
+// indices (the denser the pushes, the fewer).  The block finds where the bucket starts and ends in every
+// client's (ascending) index list, all bounds at once by groups of lanes (a
+// 32-way search for four clients, 8-way for sixteen), stages those entries in
+// LDS, dealt to the threads whatever client they come from, marks the indices
 // pushed more than once, and then gives every index to the lowest client
 // holding it, which sums all clients' values for it in client order and
 // writes p once.  The parameter writes of a block stay inside its bucket.
@@ -32,28 +32,34 @@
 
 namespace gd {
 
-constexpr int kApplyBucketShift = 15;
+constexpr uint32_t kApplyBucketShift = 15;                   // parameters of a bucket, at most (log2)
+constexpr uint32_t kApplyBucketMin = 11;                     // and at least
+constexpr uint32_t kApplyBucketEntries = 512;                // entries of a bucket, on average at most
 constexpr int kApplyLds = 2048;                              // entries of all clients staged per bucket
 constexpr int kBucketWords = (1 << kApplyBucketShift) / 32;  // one bit per index of a bucket
 
-// First position in list[lo, hi) whose value is >= x, found by the 32 lanes of
-// one half-wave together (g: lane within the half, mask: the half's lanes).
-__device__ uint32_t half_lower_bound(const uint32_t* list, uint32_t lo, uint32_t hi, uint32_t x, uint32_t g,
-                                     uint64_t mask) {
-    while (hi > lo) {
-        const uint32_t len = hi - lo;
-        if (len <= 32u) {
-            const bool below = g < len && list[lo + (g < len ? g : 0u)] < x;
-            return lo + popc64(ballot(below) & mask);
+// First position in list[0, n) whose value is >= x, found by a group of L
+// lanes together (L a power of two, g the lane within its group): L probes a
+// round.  All lanes of the wave call it; groups may search different lists.
+__device__ __forceinline__ uint32_t group_lower_bound(const uint32_t* list, uint32_t n, uint32_t x, uint32_t L, uint32_t g) {
+    const uint64_t mask = (L == 64 ? ~0ull : (1ull << L) - 1ull) << (lane_id() & ~(L - 1u));
+    uint32_t lo = 0, hi = n;
+    while (ballot(hi > lo) != 0) {
+        const uint32_t len = hi - lo, step = (len + L - 1u) / L;
+        uint64_t q = len <= L ? (uint64_t)lo + g : (uint64_t)lo + (uint64_t)(g + 1u) * step - 1u;
+        if (len > L && q >= hi) q = hi - 1u;
+        // probes rise with g, so the lanes below x form a prefix of the group
+        const bool below = q < hi && list[q] < x;
+        const uint32_t t = popc64(ballot(below) & mask);
+        if (hi > lo) {
+            if (len <= L) {
+                lo = hi = lo + t;
+            } else {
+                const uint64_t nlo = (uint64_t)lo + (uint64_t)t * step, nhi = nlo + step;
+                lo = nlo < hi ? (uint32_t)nlo : hi;
+                hi = nhi < hi ? (uint32_t)nhi : hi;
+            }
         }
-        const uint32_t step = (len + 31u) / 32u;
-        uint32_t q = lo + (g + 1u) * step - 1u;
-        if (q >= hi) q = hi - 1u;
-        // probes rise with g, so the lanes below x form a prefix of the half
-        const uint32_t t = popc64(ballot(list[q] < x) & mask);
-        const uint64_t nlo = (uint64_t)lo + (uint64_t)t * step, nhi = nlo + step;
-        lo = nlo < hi ? (uint32_t)nlo : hi;
-        hi = nhi < hi ? (uint32_t)nhi : hi;
     }
     return lo;
 }
@@ -69,143 +75,180 @@ __device__ __forceinline__ uint32_t find_u32(const uint32_t* list, uint32_t lo, 
     return a < hi && list[a] == x ? a : hi;
 }
 
-// Value of entry pos (index i) of push c: sent as is, or a quantised push's
-// centre, chosen by the entry's sign bit from the pair of its tensor or column.
-__device__ __forceinline__ float push_val(const ApplyArgs& a, uint32_t c, uint32_t pos, uint32_t i) {
-    if (a.qkind == 0) return a.val[c][pos];
-    uint32_t lo = 0, hi = a.T;  // tensor holding i: the last t with tensor_off[t] <= i
+// Layouts of at most this many tensors have their starts copied to LDS, where
+// the quantised pushes look up each entry's tensor.
+constexpr uint32_t kApplyTensors = 64;
+
+__device__ __forceinline__ void load_starts(const ApplyArgs& a, uint32_t* starts) {
+    if (a.qkind != 0 && a.T <= kApplyTensors && threadIdx.x < a.T) starts[threadIdx.x] = a.tensor_off[threadIdx.x];
+}
+
+// Centre of a quantised push's entry (index i): the entry's sign picks it from
+// the pair of its tensor or column.  starts: the tensors' first elements
+// (load_starts), or where they are many, in memory.
+__device__ __forceinline__ float push_centre(const ApplyArgs& a, const uint32_t* starts, const float* means, uint32_t i,
+                                             uint32_t neg) {
+    uint32_t lo = 0, hi = a.T;  // tensor holding i: the last t with start <= i
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (a.tensor_off[mid] <= i) lo = mid;
+        const uint32_t x = a.T <= kApplyTensors ? starts[mid] : a.tensor_off[mid];
+        if (x <= i) lo = mid;
         else hi = mid;
     }
     const uint32_t g = a.qkind == kQuantColumnMean ? a.colbase[lo] + (i - a.tensor_off[lo]) % a.columns[lo] : lo;
-    const uint32_t neg = (a.bits[c][pos >> 5] >> (pos & 31)) & 1u;
-    return a.means[c][2 * g + neg];
+    return means[2 * g + neg];
+}
+
+// Value of entry pos (index i) of push c: sent as is, or the entry's centre.
+__device__ __forceinline__ float push_val(const ApplyArgs& a, const uint32_t* starts, uint32_t c, uint32_t pos, uint32_t i) {
+    if (a.qkind == 0) return a.val[c][pos];
+    return push_centre(a, starts, a.means[c], i, (a.bits[c][pos >> 5] >> (pos & 31)) & 1u);
 }
 
 __global__ __launch_bounds__(kBlock) void k_apply(ApplyArgs a) {
-    __shared__ uint32_t rng[kMaxPushes][2];  // bucket's [begin, end) in each client's list
+    __shared__ uint32_t rng[2 * kMaxPushes];   // bucket's [begin, end) in each client's list
     __shared__ uint32_t base[kMaxPushes + 1];  // first staged entry of each client
     __shared__ uint32_t sidx[kApplyLds];
     __shared__ float sval[kApplyLds];
     __shared__ uint32_t seen[2][kBucketWords];  // [0]: index pushed at least once, [1]: more than once
-    const int tid = threadIdx.x, w = (int)wave_index(), lane = lane_id();
+    __shared__ uint32_t starts[kApplyTensors];
+    __shared__ uint16_t again[kApplyLds];  // staged entries whose index another client holds too
+    __shared__ uint32_t nagain;
+    const int tid = threadIdx.x;
     const uint32_t b = blockIdx.x;
-    const uint32_t i_lo = b << kApplyBucketShift;
-    const uint64_t i_hi64 = ((uint64_t)b + 1) << kApplyBucketShift;
+    const uint32_t i_lo = b << a.bshift;
+    const uint64_t i_hi64 = ((uint64_t)b + 1) << a.bshift;
     const uint32_t i_hi = i_hi64 < a.n ? (uint32_t)i_hi64 : a.n;
-    // 1. the bucket's range in every list: one client per wave, the two bounds
-    //    by the two half-waves
-    const uint32_t half = (uint32_t)lane >> 5, g = (uint32_t)lane & 31u;
-    const uint64_t mask = half ? 0xFFFFFFFF00000000ull : 0x00000000FFFFFFFFull;
-    for (uint32_t c = w; c < a.C; c += kWavesPerBlock) {
-        const uint32_t pos = half_lower_bound(a.idx[c], 0, a.nnz[c], half ? i_hi : i_lo, g, mask);
-        if (g == 0) rng[c][half] = pos;
+    // 1. the bucket's range in every list, all 2 C bounds at once: groups of
+    //    as many lanes as the block has for each
+    uint32_t L = 32;
+    while (L * 2 * a.C > (uint32_t)kBlock) L >>= 1;
+    {
+        const uint32_t j = tid / L;  // bound j & 1 of client j >> 1
+        const bool has = j < 2 * a.C;
+        const uint32_t c = has ? j >> 1 : 0u;
+        const uint32_t pos = group_lower_bound(a.idx[c], has ? a.nnz[c] : 0u, j & 1 ? i_hi : i_lo, L, tid & (L - 1u));
+        if (has && (tid & (L - 1u)) == 0) rng[j] = pos;
+    }
+    load_starts(a, starts);
+    if (tid == 0) nagain = 0;
+    for (uint32_t q = tid; q < (1u << a.bshift) / 32u; q += kBlock) {
+        seen[0][q] = 0;
+        seen[1][q] = 0;
     }
     __syncthreads();
-    if (tid == 0) {
-        uint32_t acc = 0;
-        for (uint32_t c = 0; c < a.C; ++c) {
-            base[c] = acc;
-            acc += rng[c][1] - rng[c][0];
-        }
-        base[a.C] = acc;
+    if (tid < kWave) {
+        // (a list out of order may end before it begins)
+        const uint32_t cnt = (uint32_t)tid < a.C && rng[2 * tid + 1] > rng[2 * tid] ? rng[2 * tid + 1] - rng[2 * tid] : 0u;
+        const uint32_t incl = wave_incl_scan(cnt);
+        base[tid] = incl - cnt;  // (for tid >= C: the total)
+        if (tid == kWave - 1) base[kWave] = incl;
     }
     __syncthreads();
-    const uint32_t total = base[a.C];
+    const uint32_t total = base[kMaxPushes];
     if (total == 0) return;
-    const bool staged = total <= (uint32_t)kApplyLds;
-    // 2. stage the bucket's entries (index, value) of every client, and mark
-    //    the indices pushed more than once
-    if (staged) {
-        for (uint32_t q = tid; q < 2u * kBucketWords; q += kBlock) (&seen[0][0])[q] = 0;
-        __syncthreads();
-        for (uint32_t c = 0; c < a.C; ++c) {
-            const uint32_t r0 = rng[c][0], cnt = rng[c][1] - r0, o = base[c];
-            for (uint32_t q = tid; q < cnt; q += kBlock) {
-                const uint32_t ii = a.idx[c][r0 + q];
-                const uint32_t off = ii - i_lo, bit = 1u << (off & 31);
-                // an index outside the bucket (a list out of order) is skipped
-                sidx[o + q] = off < i_hi - i_lo ? ii : kNoKey;
-                sval[o + q] = push_val(a, c, r0 + q, ii);
-                if (off < i_hi - i_lo && (atomicOr(&seen[0][off >> 5], bit) & bit)) atomicOr(&seen[1][off >> 5], bit);
-            }
-        }
-        __syncthreads();
-    }
-    // 3. each entry: skip it if a lower client holds the same index, else sum
-    //    every client's value for it in client order and update p once (an
-    //    index pushed once needs no search).  When staged, a thread settles all
-    //    its entries first and then reads all its parameters at once, so their
-    //    latencies overlap instead of adding up.
-    if (staged) {
+    if (total <= (uint32_t)kApplyLds) {
+        // 2. stage the bucket's entries (index, value) of every client, dealt
+        //    to the threads in order: entry e belongs to the last client whose
+        //    first entry is at or before it.  Indices, values or sign words of
+        //    all a thread's entries are in flight together.
         constexpr int kPer = kApplyLds / kBlock;
-        uint32_t pi[kPer];
-        float pstep[kPer];
-        bool pv[kPer];
+        uint32_t cl[kPer], pi[kPer], bits[kPer];
+        float pv[kPer];
 #pragma unroll
         for (int t = 0; t < kPer; ++t) {
             const uint32_t e = tid + t * kBlock;
-            pv[t] = false;
-            pi[t] = i_lo;  // a valid parameter index for the unconditional load below
-            pstep[t] = 0.0f;
-            if (e < total && sidx[e] != kNoKey) {
-                uint32_t c = 0;
-                while (base[c + 1] <= e) ++c;  // client of staged entry e
-                const uint32_t i = sidx[e];
-                const uint32_t off = i - i_lo;
-                const bool once = (seen[1][off >> 5] & (1u << (off & 31))) == 0;
-                bool owner = true;
-                for (uint32_t cc = 0; cc < c && owner && !once; ++cc)
-                    owner = find_u32(sidx, base[cc], base[cc + 1], i) == base[cc + 1];
-                if (owner) {
-                    float sum = 0.0f + sval[e];
-                    for (uint32_t cc = c + 1; cc < a.C && !once; ++cc) {
-                        const uint32_t hit = find_u32(sidx, base[cc], base[cc + 1], i);
-                        if (hit != base[cc + 1]) sum = sum + sval[hit];
-                    }
-                    pv[t] = true;
-                    pi[t] = i;
-                    pstep[t] = a.lr * sum;
-                }
-            }
+            cl[t] = kNoKey;
+            pi[t] = kNoKey;
+            pv[t] = 0.0f;
+            bits[t] = 0;
+            if (e >= total) continue;
+            uint32_t c = 0;
+#pragma unroll
+            for (uint32_t st = kMaxPushes / 2; st > 0; st >>= 1)
+                if (base[c + st] <= e) c += st;  // (clients past the last have no entry: base is the total)
+            const uint32_t pos = rng[2 * c] + (e - base[c]);
+            cl[t] = c;
+            pi[t] = a.idx[c][pos];
+            if (a.qkind == 0) pv[t] = a.val[c][pos];
+            else bits[t] = a.bits[c][pos >> 5] >> (pos & 31);
         }
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            const uint32_t e = tid + t * kBlock;
+            if (e >= total) continue;
+            const uint32_t off = pi[t] - i_lo, bit = 1u << (off & 31);
+            // an index outside the bucket (a list out of order) is skipped
+            if (off >= i_hi - i_lo) pi[t] = kNoKey;
+            else if (a.qkind != 0) pv[t] = push_centre(a, starts, a.means[cl[t]], pi[t], bits[t] & 1u);
+            sidx[e] = pi[t];
+            sval[e] = pv[t];
+            if (pi[t] != kNoKey && (atomicOr(&seen[0][off >> 5], bit) & bit)) atomicOr(&seen[1][off >> 5], bit);
+        }
+        __syncthreads();
+        // 3. an index pushed once takes its value; a thread reads the
+        //    parameters of all its entries at once, so that their latencies
+        //    overlap.  The entries of the others are listed and dealt to the
+        //    threads anew (a wave that met a few of them among its own entries
+        //    would wait for their searches each time): an entry is skipped if
+        //    a lower client holds its index, else it sums every client's value
+        //    in client order.
         float pold[kPer];
 #pragma unroll
-        for (int t = 0; t < kPer; ++t) pold[t] = a.p[pi[t]];
+        for (int t = 0; t < kPer; ++t) {
+            pold[t] = 0.0f;
+            if (pi[t] == kNoKey) continue;
+            const uint32_t off = pi[t] - i_lo;
+            if (seen[1][off >> 5] & (1u << (off & 31))) {
+                again[atomicAdd(&nagain, 1u)] = (uint16_t)(tid + t * kBlock);
+                pi[t] = kNoKey;
+            } else {
+                pold[t] = a.p[pi[t]];
+            }
+        }
+        __syncthreads();
+        for (uint32_t d = tid; d < nagain; d += kBlock) {
+            const uint32_t e = again[d], i = sidx[e];
+            uint32_t c = 0;
 #pragma unroll
-        for (int t = 0; t < kPer; ++t)
-            if (pv[t]) a.p[pi[t]] = pold[t] - pstep[t];
+            for (uint32_t st = kMaxPushes / 2; st > 0; st >>= 1)
+                if (base[c + st] <= e) c += st;
+            const float old = a.p[i];
+            bool owner = true;
+            for (uint32_t cc = 0; cc < c && owner; ++cc)
+                owner = find_u32(sidx, base[cc], base[cc + 1], i) == base[cc + 1];
+            if (!owner) continue;
+            float sum = 0.0f + sval[e];
+            for (uint32_t cc = c + 1; cc < a.C; ++cc) {
+                const uint32_t hit = find_u32(sidx, base[cc], base[cc + 1], i);
+                if (hit != base[cc + 1]) sum = sum + sval[hit];
+            }
+            const float step = a.lr * sum;
+            a.p[i] = old - step;
+        }
+#pragma unroll
+        for (int t = 0; t < kPer; ++t) {
+            if (pi[t] == kNoKey) continue;
+            const float sum = 0.0f + pv[t], step = a.lr * sum;
+            a.p[pi[t]] = pold[t] - step;
+        }
         return;
     }
+    // More entries than the block can stage: each reads the lists as they lie.
     for (uint32_t e = tid; e < total; e += kBlock) {
         uint32_t c = 0;
-        while (base[c + 1] <= e) ++c;  // client of staged entry e
+        while (base[c + 1] <= e) ++c;  // client of entry e
         const uint32_t q = e - base[c];
-        const uint32_t i = staged ? sidx[e] : a.idx[c][rng[c][0] + q];
+        const uint32_t i = a.idx[c][rng[2 * c] + q];
         if (i - i_lo >= i_hi - i_lo) continue;  // outside the bucket: a list out of order
         bool owner = true;
-        for (uint32_t cc = 0; cc < c && owner; ++cc) {
-            const uint32_t hit = staged ? find_u32(sidx, base[cc], base[cc + 1], i)
-                                        : find_u32(a.idx[cc], rng[cc][0], rng[cc][1], i);
-            owner = staged ? hit == base[cc + 1] : hit == rng[cc][1];
-        }
+        for (uint32_t cc = 0; cc < c && owner; ++cc)
+            owner = find_u32(a.idx[cc], rng[2 * cc], rng[2 * cc + 1], i) == rng[2 * cc + 1];
         if (!owner) continue;
-        float s = 0.0f;
-        for (uint32_t cc = 0; cc < a.C; ++cc) {
-            if (cc < c) continue;
-            if (cc == c) {
-                s = s + (staged ? sval[e] : push_val(a, c, rng[c][0] + q, i));
-                continue;
-            }
-            if (staged) {
-                const uint32_t hit = find_u32(sidx, base[cc], base[cc + 1], i);
-                if (hit != base[cc + 1]) s = s + sval[hit];
-            } else {
-                const uint32_t hit = find_u32(a.idx[cc], rng[cc][0], rng[cc][1], i);
-                if (hit != rng[cc][1]) s = s + push_val(a, cc, hit, i);
-            }
+        float s = 0.0f + push_val(a, starts, c, rng[2 * c] + q, i);
+        for (uint32_t cc = c + 1; cc < a.C; ++cc) {
+            const uint32_t hit = find_u32(a.idx[cc], rng[2 * cc], rng[2 * cc + 1], i);
+            if (hit != rng[2 * cc + 1]) s = s + push_val(a, starts, cc, hit, i);
         }
         const float step = a.lr * s;
         a.p[i] = a.p[i] - step;
@@ -241,29 +284,7 @@ constexpr int kApplyTileThreads = 256;
 constexpr int kApplyTileVecs = (int)kApplyTileLen / 4 / kApplyTileThreads;        // 16-byte vectors per thread
 constexpr int kApplyTileEntries = 2;                                                // entries per thread per round
 constexpr uint32_t kApplyTileRound = (uint32_t)kApplyTileEntries * kApplyTileThreads;
-static_assert(kMaxPushes <= kWave, "one lane per client holds its range");
-
-// push_val for a client index that differs between lanes: the client's sign
-// bits and centres are picked by comparing it with each client in turn.
-__device__ __forceinline__ float push_val_lanes(const ApplyArgs& a, uint32_t c, uint32_t pos, uint32_t i) {
-    const uint32_t* bits = a.bits[0];
-    const float* means = a.means[0];
-    for (uint32_t cc = 1; cc < a.C; ++cc) {
-        if (c == cc) {
-            bits = a.bits[cc];
-            means = a.means[cc];
-        }
-    }
-    uint32_t lo = 0, hi = a.T;  // tensor holding i
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (a.tensor_off[mid] <= i) lo = mid;
-        else hi = mid;
-    }
-    const uint32_t g = a.qkind == kQuantColumnMean ? a.colbase[lo] + (i - a.tensor_off[lo]) % a.columns[lo] : lo;
-    const uint32_t neg = (bits[pos >> 5] >> (pos & 31)) & 1u;
-    return means[2 * g + neg];
-}
+static_assert(kMaxPushes == kWave, "one lane per client holds its range");
 
 // The bounds table of the streaming form: row c holds, for every tile
 // boundary B_b (b * kApplyTileLen for b < tiles, n for b = tiles), the first
@@ -296,11 +317,13 @@ __global__ __launch_bounds__(kBlock) void k_apply_bounds(ApplyArgs a, uint32_t t
 __global__ __launch_bounds__(kApplyTileThreads) void k_apply_tile(ApplyArgs a) {
     __shared__ __align__(16) float sum[kApplyTileLen];      // per parameter of the tile
     __shared__ uint32_t touched[kApplyTileLen / 32];       // pushed at least once
+    __shared__ uint32_t starts[kApplyTensors];
     const int tid = threadIdx.x, lane = lane_id();
     const uint32_t b = blockIdx.x, C = a.C;
     const uint32_t i_lo = b << kApplyTileShift;
     const bool whole = (uint64_t)i_lo + kApplyTileLen <= a.n;  // the same in every thread
     const uint32_t len = whole ? kApplyTileLen : a.n - i_lo;
+    load_starts(a, starts);  // (read after the first barrier below)
     // The tile's range in the list of client `lane` (lanes >= C: none), from
     // the bounds table and clamped to the list, so that any table content
     // stays inside it.  Every wave reads it, so no barrier is needed for it.
@@ -344,7 +367,7 @@ __global__ __launch_bounds__(kApplyTileThreads) void k_apply_tile(ApplyArgs a) {
     for (uint32_t e0 = 0; e0 < total; e0 += kApplyTileRound) {
         // this thread's entries e = e0 + tid + kApplyTileThreads k: offset in
         // the tile, client and value, all loaded at once
-        uint32_t off[kApplyTileEntries], cl[kApplyTileEntries];
+        uint32_t off[kApplyTileEntries], cl[kApplyTileEntries], bits[kApplyTileEntries];
         float val[kApplyTileEntries];
 #pragma unroll
         for (int k = 0; k < kApplyTileEntries; ++k) {
@@ -353,11 +376,11 @@ __global__ __launch_bounds__(kApplyTileThreads) void k_apply_tile(ApplyArgs a) {
             const uint32_t* ip = a.idx[0];
             const float* vp = a.val[0];
             for (uint32_t cc = 1; cc < C; ++cc) {
-                const uint32_t bc = lane_value(base, (int)cc);
+                const uint32_t bc = lane_value(base, (int)cc), rc = lane_value(r0, (int)cc);
                 if (e >= bc) {
                     c = cc;
                     first = bc;
-                    at = lane_value(r0, (int)cc);
+                    at = rc;
                     ip = a.idx[cc];
                     vp = a.val[cc];
                 }
@@ -365,15 +388,22 @@ __global__ __launch_bounds__(kApplyTileThreads) void k_apply_tile(ApplyArgs a) {
             cl[k] = kNoKey;
             off[k] = kNoKey;
             val[k] = 0.0f;
+            bits[k] = 0;
             if (e < total) {
                 const uint32_t pos = at + (e - first);
                 const uint32_t i = ip[pos];
                 cl[k] = c;
                 off[k] = i - i_lo;  // outside the tile (a list out of order): skipped below
-                val[k] = a.qkind == 0 ? vp[pos] : push_val_lanes(a, c, pos, i);
+                if (a.qkind == 0) val[k] = vp[pos];
+                else bits[k] = a.bits[c][pos >> 5] >> (pos & 31);
             }
         }
         __syncthreads();  // sums cleared (first round), or the previous round's turns done
+        if (a.qkind != 0) {
+#pragma unroll
+            for (int k = 0; k < kApplyTileEntries; ++k)
+                if (off[k] < len) val[k] = push_centre(a, starts, a.means[cl[k]], i_lo + off[k], bits[k] & 1u);
+        }
         for (uint32_t t = 0; t < C; ++t) {
             if (t > 0) __syncthreads();  // the previous client's turn done
 #pragma unroll
@@ -461,15 +491,30 @@ hipError_t launch_apply(const ApplyArgs& a, uint32_t max_nnz, hipStream_t st) {
     if (a.C == 0 || max_nnz == 0 || a.n == 0) return hipSuccess;
     uint64_t total = 0;
     for (uint32_t c = 0; c < a.C; ++c) total += a.nnz[c];
-    // Streaming reads every line of the shard: it pays once the entries touch
-    // most lines (one entry per 64 parameters touches about 40% of them).
-    // Each client adds a turn of barriers to every tile and a comparison to
-    // every entry's client lookup, so many clients stay with the scattered
-    // form unless the form is forced.
+    // Streaming reads every line of the shard, in order; scattered reads and
+    // writes words, and searches for the indices that several clients hold.
+    // The line lies where the two measure alike, over indices spread evenly
+    // and over indices in a sixteenth of the rows of 1,000 (in this order, us
+    // scattered / streaming).  One client: 9.7M parameters, an entry per 32:
+    // 13.0 / 16.3 and 10.8 / 13.4, per 16: 15.6 / 18.4; 37M, per 32: 40 / 57 and
+    // 20 / 37, per 16: 72 / 68.  Four: 9.7M, per 64: 15.4 / 17.7 and 16.1 / 14.4,
+    // per 32: 17.3 / 18.3 and 54.9 / 16.2; 37M, per 64: 28 / 45 and 21 / 37, per
+    // 32: 47 / 58 and 76 / 40.  Sixteen: 9.7M, per 256: 19.9 / 24.1 and 22.9 /
+    // 22.4, per 64: 27.6 / 25.1 and 35.9 / 22.5; 37M, per 64: 38 / 56 and 42 / 43,
+    // per 32: 66 / 63 and 225 / 49.
     const int form = g_apply_form.load();
     const bool aligned = (reinterpret_cast<uintptr_t>(a.p) & 15u) == 0;
-    const bool dense = total * 64u >= a.n;
-    const bool stream = aligned && form != 1 && (form == 2 || (dense && a.C <= 8u));
+    const bool cached = a.n <= (1u << 24);  // the shard stays in the caches (64 MiB)
+    const uint64_t sparse = a.C == 1u ? 24u : !cached ? 48u : a.C <= 8u ? 64u : 128u;
+    bool stream = aligned && form != 1 && (form == 2 || total * sparse >= a.n);
+    if (stream && form != 2 && a.C > 8u) {
+        // A captured call of more than 8 clients is scattered, so that no
+        // first call is needed before the capture, and no replay depends on a
+        // table that a later call on the stream may replace.
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        stream = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!stream) (void)hipGetLastError();
+    }
     if (stream) {
         const uint32_t tiles = (uint32_t)(((uint64_t)a.n + kApplyTileLen - 1) >> kApplyTileShift);
         std::lock_guard<std::mutex> lk(g_tab_mu);
@@ -487,8 +532,11 @@ hipError_t launch_apply(const ApplyArgs& a, uint32_t max_nnz, hipStream_t st) {
         }
         (void)hipGetLastError();  // no table: the scattered form below
     }
-    const uint32_t buckets = (uint32_t)(((uint64_t)a.n + (1u << kApplyBucketShift) - 1) >> kApplyBucketShift);
-    hipLaunchKernelGGL(k_apply, dim3(buckets), dim3(kBlock), 0, st, a);
+    ApplyArgs b = a;
+    b.bshift = kApplyBucketShift;
+    while (b.bshift > kApplyBucketMin && (total << b.bshift) > (uint64_t)kApplyBucketEntries * a.n) --b.bshift;
+    const uint32_t buckets = (uint32_t)(((uint64_t)a.n + (1ull << b.bshift) - 1) >> b.bshift);
+    hipLaunchKernelGGL(k_apply, dim3(buckets), dim3(kBlock), 0, st, b);
     return hipGetLastError();
 }
 

@@ -230,6 +230,7 @@ struct ApplyArgs {
     uint32_t T;
     const uint32_t* columns;     // [T]
     const uint32_t* colbase;     // [T + 1]
+    uint32_t bshift;             // scattered form: log2 of a bucket's parameters
     // streaming form: first position in each client's list of every tile
     // boundary (row c at tab + c * tstride)
     const uint32_t* tab;

@@ -1,0 +1,87 @@
+"""Server-side applies over numbers of clients and densities, both forms and
+the one chosen per call, against the oracle: one lane group per list bound (1
+to 64 clients), bucket sizes (2^11 to 2^15 parameters, by density), buckets of
+more entries than are staged, indices that several clients share, layouts on
+either side of the tensor starts kept on chip, and a captured call of many
+clients on a stream that no call has used before."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1704_05021_amd import gd
+from parity import bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _pushes(rng, n, clients, density, shared):
+    """Ascending unique indices per client; every client also holds the `shared` indices."""
+    idx = []
+    common = rng.integers(0, n, shared)
+    for c in range(clients):
+        own = rng.integers(0, n, int(n * density / clients) if c % 5 != 3 else 0)  # some lists (nearly) empty
+        idx.append(np.unique(np.concatenate([own, common, [n - 1] if c % 2 else []])).astype(np.uint32))
+    return idx, [rng.normal(0, 1, i.size).astype(np.float32) for i in idx]
+
+
+def _same(got, want):
+    assert np.array_equal(bits(got.cpu().numpy()), bits(want))
+
+
+# (n, density): around the sizes of a bucket (15 to 11 bits), all entries
+# unstaged (a bucket of 2^11 parameters that every client holds), last bucket short
+@pytest.mark.parametrize("n,density", [(1, 1.0), (2_049, 4.0), (32_767, 1 / 64), (32_769, 1 / 63), (70_001, 1 / 32),
+                                       (70_001, 1 / 8), (70_001, 1 / 3), (300_007, 1 / 128), (70_001, 16.0)])
+@pytest.mark.parametrize("clients", [1, 4, 5, 8, 9, 16, 17, 33, 64])
+def test_sparse(clients, n, density, apply_form):
+    rng = np.random.default_rng(clients * 1000 + n % 997)
+    idx, val = _pushes(rng, n, clients, density, n // 300)
+    p0 = rng.normal(0, 1, n).astype(np.float32)
+    want = oracle.apply_sparse(p0, idx, val, 0.3)
+    ti, tv = [torch.from_numpy(i.view(np.int32)).cuda() for i in idx], [torch.from_numpy(v).cuda() for v in val]
+    p = torch.from_numpy(p0).cuda()
+    gd.apply_sparse(p, ti, tv, 0.3)
+    _same(p, want)
+    gd.debug_apply_form(0)
+    p = torch.from_numpy(p0).cuda()
+    gd.apply_sparse(p, ti, tv, 0.3)
+    _same(p, want)
+
+
+@pytest.mark.parametrize("tensors", [1, 64, 65])
+@pytest.mark.parametrize("clients", [2, 16])
+def test_quantised(clients, tensors, apply_form):
+    rng = np.random.default_rng(tensors)
+    n = 50_003
+    off = [0] + np.sort(rng.integers(0, n + 1, tensors - 1)).tolist() + [n]
+    outs = [oracle.compress(rng.normal(0, 1, n).astype(np.float32), np.zeros(n, np.float32), off, 0.97, per_tensor=False,
+                            quant=1) for _ in range(clients)]
+    p0 = rng.normal(0, 1, n).astype(np.float32)
+    want = oracle.apply_quantised(p0, off, [o.idx for o in outs], [o.sign_bits for o in outs], [o.means for o in outs], 1, 0.5)
+    p = torch.from_numpy(p0).cuda()
+    gd.Compressor(off).apply_quantised(p, [torch.from_numpy(o.idx.view(np.int32)).cuda() for o in outs],
+                                       [torch.from_numpy(o.sign_bits.view(np.int32)).cuda() for o in outs],
+                                       [torch.from_numpy(o.means).cuda() for o in outs], 1, 0.5)
+    _same(p, want)
+
+
+def test_captured_many_clients():
+    rng = np.random.default_rng(3)
+    n = 90_001
+    idx, val = _pushes(rng, n, 12, 1 / 4, 100)
+    ti, tv = [torch.from_numpy(i.view(np.int32)).cuda() for i in idx], [torch.from_numpy(v).cuda() for v in val]
+    p0 = rng.normal(0, 1, n).astype(np.float32)
+    p = torch.from_numpy(p0).cuda()
+    stream = torch.cuda.Stream()  # no call has been made on it: no table of its own
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        gd.apply_sparse(p, ti, tv, 0.3)
+    want = p0
+    for _ in range(4):
+        graph.replay()
+        want = oracle.apply_sparse(want, idx, val, 0.3)
+        _same(p, want)
+        q = torch.from_numpy(want).cuda()
+        gd.apply_sparse(q, ti, tv, 0.3)  # eager work between the replays
+        _same(q, oracle.apply_sparse(want, idx, val, 0.3))
