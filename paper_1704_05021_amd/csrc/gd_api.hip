@@ -131,6 +131,11 @@ struct DenseTimer {
 // 1-bit quantisation of the sent list.  k_total is the host-known output size
 // (exact threshold), or under a sampled threshold the capacity, a bound the
 // device-side count stays within.
+gd::ColSums col_sums(const gd_ctx* ctx, gd_quant quant) {
+    if (quant != GD_QUANT_COLUMN_MEAN) return {};
+    return {ctx->cols.csum, ctx->cols.ccnt, 2 * (uint64_t)ctx->cols.groups};
+}
+
 gd_status run_quant(gd_ctx* ctx, float* residual, bool per, uint32_t ppm, bool direct, bool sampled, gd_quant quant,
                     uint64_t k_total, const gd_sparse* out, hipStream_t st) {
     if (quant == GD_QUANT_NONE) return GD_OK;
@@ -239,6 +244,7 @@ gd_status run_after_bracket(gd_ctx* ctx, const float* grad, const float* base, f
     ea.tensor_counts = out->tensor_counts;
     ea.capacity = out->capacity;
     ea.qkind = (uint32_t)quant;
+    ea.cols = col_sums(ctx, quant);
     if (gd::launch_layout(ca, st) != hipSuccess) return GD_ERR_HIP;
     if (gd::launch_candidates(ca, ea, quant != GD_QUANT_NONE, ctx->max_tiles, st) != hipSuccess) return GD_ERR_HIP;
     return run_quant(ctx, residual, per, ppm, false, sampled, quant, k_total, out, st);
@@ -288,6 +294,7 @@ gd_status compress_exact(gd_ctx* ctx, const float* grad, const float* base, floa
         a.idx = out->idx;
         a.val = out->val;
         a.capacity = out->capacity;
+        a.cols = col_sums(ctx, quant);
         const DenseTimer timer(ctx);
         if (launch_direct(a, !residual ? 2 : base ? 1 : 0, st, timer.t0, timer.t1) != hipSuccess) return GD_ERR_HIP;
         timer.launched(ctx);

@@ -785,8 +785,10 @@ __global__ __launch_bounds__(kBlock) void k_radix(CandArgs a) {
 
 __global__ __launch_bounds__(kBlock) void k_count(CandArgs a, EmitArgs o) { phase_count(a, o); }
 
-template <bool QUANT>
+// COLUMN: with the column sums cleared for the quantisation behind it.
+template <bool QUANT, bool COLUMN>
 __global__ __launch_bounds__(kBlock) void k_emit(CandArgs a, EmitArgs o) {
+    if (COLUMN) clear_col_sums(o.cols);
     phase_emit<QUANT>(a, o);
 }
 
@@ -803,8 +805,9 @@ hipError_t launch_candidates(const CandArgs& a, const EmitArgs& o, bool quant, u
         hipLaunchKernelGGL(k_radix<2>, gt, b, 0, st, a);
     }
     if (!a.sampled) hipLaunchKernelGGL(k_count, gt, b, 0, st, a, o);  // under a sampled threshold every candidate is sent
-    if (quant) hipLaunchKernelGGL(k_emit<true>, gt, b, 0, st, a, o);
-    else hipLaunchKernelGGL(k_emit<false>, gt, b, 0, st, a, o);
+    if (o.cols.n) hipLaunchKernelGGL((k_emit<true, true>), gt, b, 0, st, a, o);
+    else if (quant) hipLaunchKernelGGL((k_emit<true, false>), gt, b, 0, st, a, o);
+    else hipLaunchKernelGGL((k_emit<false, false>), gt, b, 0, st, a, o);
     return hipGetLastError();
 }
 

@@ -733,6 +733,7 @@ template <int UPW, bool PULL>
 __global__ __launch_bounds__(kDirectThreads) void k_demit(DirectArgs a) {
     __shared__ __align__(16) uint32_t h[kSelBins];
     __shared__ __align__(16) uint32_t lds[kResolveLds<kDirectThreads>];
+    clear_col_sums(a.cols);
     direct_emit<kDirectThreads, UPW, PULL>(a, h, lds);
 }
 

@@ -142,6 +142,21 @@ struct PieceInfo {
     uint32_t kmax;
 };
 
+// Column sums and counts that the emitting kernel clears for the passes behind
+// it (n = 0 but under column-wise centres).
+struct ColSums {
+    double* sum;
+    uint32_t* cnt;
+    uint64_t n;  // two per column group
+};
+
+__device__ __forceinline__ void clear_col_sums(const ColSums& c) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n; i += (uint64_t)gridDim.x * blockDim.x) {
+        c.sum[i] = 0.0;
+        c.cnt[i] = 0;
+    }
+}
+
 struct DirectArgs {
     const float* grad;   // the inputs of the first pass
     const float* base;
@@ -165,6 +180,7 @@ struct DirectArgs {
     uint32_t* idx;
     float* val;
     uint64_t capacity;
+    ColSums cols;
 };
 
 // 1-bit centres (Section 5.4): per-tensor sign means, the dropping threshold,
@@ -177,6 +193,7 @@ struct EmitArgs {
     uint32_t* tensor_counts;
     uint64_t capacity;
     uint32_t qkind;             // 0 or a kQuant* kind
+    ColSums cols;
 };
 
 struct QuantArgs {
@@ -203,7 +220,7 @@ struct QuantArgs {
     const uint32_t* colbase;
     uint32_t sampled;           // 1 under a sampled threshold: the count is k_total at most, qbase[T] exactly
     uint32_t groups;            // column groups (column-wise centres)
-    double* csum;               // [2 * groups] column sums (positive, negative), zero on entry, cleared after use
+    double* csum;               // [2 * groups] column sums (positive, negative), cleared by the emitting kernel
     uint32_t* ccnt;             // [2 * groups] column counts, likewise
     uint32_t direct;            // after the direct form, which keeps no tile sums:
     double* tq;                 // [slices * 4 + 4 T] sums and counts of the sent entries, per slice and tensor

@@ -17,12 +17,14 @@
 // per touched column).  The sent bits are packed LSB-first, 32 per word,
 // and residual[idx] becomes acc - centre.
 
+#include <algorithm>
+
 #include "gd_kernels.h"
 
 namespace gd {
 
-constexpr uint32_t kColSlice = 4096;  // sent entries per column-sum block
-constexpr int kColLds = 2048;         // most columns a block sums in LDS (48 KB)
+// Sent entries up to which column sums take slices of 256, of 1,024 and of 2,048.
+constexpr uint64_t kColTinyK = 1u << 16, kColSmallK = 1u << 18, kColMidK = 1u << 20;
 
 // Zeros tensor u keeps in the zero mode (every candidate kept, plus zeros):
 // its kept count less its candidates; 0 outside the zero mode.
@@ -243,80 +245,116 @@ __global__ __launch_bounds__(kMeansThreads) void k_dmeans(QuantArgs q, uint32_t 
     }
 }
 
-// Column sums of the sent entries, per sign.  Each block takes a slice of
-// kColSlice consecutive output slots and walks the tensors it touches; for a
-// tensor of at most kColLds columns it sums the slice in LDS first (fp64 LDS
-// atomics) and then adds each touched column to the global sums once, so a
-// column's global atomics number its tensor's slices rather than its entries.
-// Wider tensors spread their entries over many columns and add directly.
-__global__ __launch_bounds__(kBlock) void k_colsum(QuantArgs q) {
-    __shared__ double ls[2 * kColLds];
-    __shared__ uint32_t lc[2 * kColLds];
+// Column sums of the sent entries, per sign, with the first output slot of
+// each tensor where one block can find them on the way (T <= kColLocalT).  Each
+// block takes a slice of PER * kBlock consecutive output slots, every thread
+// PER of them, loaded at once.  A tensor with at least as many entries in the
+// slice as columns is summed in LDS first (fp64 LDS atomics), each touched
+// column then added to the global sums once; the entries of the others, few to
+// a column, are added directly.  Bound by the chain of loads, then the global
+// atomics (about 16 G/s).  It took 16.8 us for 21,000 entries of a ragged 21M-element
+// layout in slices of 4,096, one entry after another, and 27.0 with the passes
+// for the first slots, the centres and the values; now 6.8 and 10.7.
+constexpr uint32_t kColLocalT = kBlock - 1;
+constexpr uint32_t kCols = 2048;  // most columns summed in LDS (48 KB)
+
+template <int PER>
+__global__ __launch_bounds__(kBlock) void k_colsum(QuantArgs q, uint32_t have_base) {
+    constexpr uint32_t kSlice = PER * kBlock;
+    __shared__ double ls[2 * kCols];
+    __shared__ uint32_t lc[2 * kCols];
+    __shared__ uint32_t first[kBlock], scan[kBlock / kWave + 1];
     const int tid = threadIdx.x;
-    const uint32_t total = q.qbase[q.T];
-    const uint64_t j0 = (uint64_t)blockIdx.x * kColSlice;
+    const uint64_t j0 = (uint64_t)blockIdx.x * kSlice;
+    float x[PER];
+    uint32_t ix[PER], ten[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint64_t at = j0 + i * kBlock + tid;
+        x[i] = at < q.k_total ? q.val[at] : 0.0f;
+        ix[i] = at < q.k_total ? q.idx[at] : 0u;
+    }
+    if (!have_base) {
+        uint32_t all;
+        const uint32_t excl = block_excl_scan<kBlock>((uint32_t)tid < q.T ? q.tensor_counts[tid] : 0u, scan, &all);
+        first[tid] = excl;
+        if (blockIdx.x == 0 && (uint32_t)tid <= q.T) q.qbase[tid] = excl;
+        __syncthreads();
+    }
+    const auto base = [&](uint32_t t) { return have_base ? q.qbase[t] : first[t]; };
+    const uint32_t total = base(q.T);
     if (j0 >= total) return;
-    const uint32_t j1 = j0 + kColSlice < total ? (uint32_t)j0 + kColSlice : total;
-    uint32_t lo = 0, hi = q.T;  // tensor of slot j0: the last t with qbase[t] <= j0
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (q.qbase[mid] <= j0) lo = mid;
-        else hi = mid;
+    const uint32_t j1 = j0 + kSlice < total ? (uint32_t)j0 + kSlice : total;
+    // tensor of slot j: the last t with base(t) <= j
+    const auto tensor_at = [&](uint32_t j) {
+        uint32_t lo = 0, hi = q.T;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (base(mid) <= j) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint64_t at = j0 + i * kBlock + tid;
+        ten[i] = at < j1 ? tensor_at((uint32_t)at) : kNoKey;
     }
-    uint32_t t = lo;
-    for (uint32_t j = (uint32_t)j0; j < j1;) {  // block-uniform walk over the tensors of the slice
-        while (q.qbase[t + 1] <= j) ++t;
-        const uint32_t e = q.qbase[t + 1] < j1 ? q.qbase[t + 1] : j1;
-        const uint32_t C = q.columns[t], cb = 2 * q.colbase[t], off = q.tensor_off[t];
-        const bool local = C <= (uint32_t)kColLds;
-        if (local) {
-            for (uint32_t i = tid; i < 2 * C; i += kBlock) {
-                ls[i] = 0.0;
-                lc[i] = 0;
+    const uint32_t t0 = tensor_at((uint32_t)j0), t1 = tensor_at(j1 - 1);
+    // (block-uniform; of more tensors than this few can qualify)
+    for (uint32_t t = t0; t <= t1 && t1 - t0 < 16; ++t) {
+        const uint32_t b = base(t), e = base(t + 1);
+        const uint32_t n = (e < j1 ? e : j1) - (b > (uint32_t)j0 ? b : (uint32_t)j0);  // (no entry: 0)
+        const uint32_t C = q.columns[t];
+        if (C > kCols || C > n) continue;
+        const uint32_t cb = 2 * q.colbase[t], off = q.tensor_off[t];
+        for (uint32_t i = tid; i < 2 * C; i += kBlock) {
+            ls[i] = 0.0;
+            lc[i] = 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (ten[i] != t) continue;
+            const uint32_t sl = 2 * ((ix[i] - off) % C) + (x[i] < 0.0f ? 1u : 0u);
+            unsafeAtomicAdd(&ls[sl], (double)x[i]);
+            atomicAdd(&lc[sl], 1u);
+            ten[i] = kNoKey;
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < 2 * C; i += kBlock)
+            if (lc[i]) {
+                unsafeAtomicAdd(&q.csum[cb + i], ls[i]);
+                atomicAdd(&q.ccnt[cb + i], lc[i]);
             }
-            __syncthreads();
-        }
-        for (uint32_t x = j + tid; x < e; x += kBlock) {
-            const float v = q.val[x];
-            const uint32_t sl = 2 * ((q.idx[x] - off) % C) + (v < 0.0f ? 1u : 0u);
-            if (local) {
-                unsafeAtomicAdd(&ls[sl], (double)v);
-                atomicAdd(&lc[sl], 1u);
-            } else {
-                unsafeAtomicAdd(&q.csum[cb + sl], (double)v);
-                atomicAdd(&q.ccnt[cb + sl], 1u);
-            }
-        }
-        if (local) {
-            __syncthreads();
-            for (uint32_t i = tid; i < 2 * C; i += kBlock)
-                if (lc[i]) {
-                    unsafeAtomicAdd(&q.csum[cb + i], ls[i]);
-                    atomicAdd(&q.ccnt[cb + i], lc[i]);
-                }
-            __syncthreads();
-        }
-        j = e;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint32_t t = ten[i];
+        if (t == kNoKey) continue;
+        const uint32_t sl = 2 * (q.colbase[t] + (ix[i] - q.tensor_off[t]) % q.columns[t]) + (x[i] < 0.0f ? 1u : 0u);
+        unsafeAtomicAdd(&q.csum[sl], (double)x[i]);
+        atomicAdd(&q.ccnt[sl], 1u);
     }
 }
 
-// Column-wise centres from the column sums, which are cleared for the next call.
-__global__ __launch_bounds__(kBlock) void k_colmeans(QuantArgs q) {
-    const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
-    if (g >= q.groups) return;
-    const double sp = q.csum[2 * g + 0], sn = q.csum[2 * g + 1];
-    const uint32_t np = q.ccnt[2 * g + 0], nn = q.ccnt[2 * g + 1];
-    q.means[2 * g + 0] = np ? (float)(sp / (double)np) : 0.0f;
-    q.means[2 * g + 1] = nn ? (float)(sn / (double)nn) : 0.0f;
-    q.csum[2 * g + 0] = 0.0;
-    q.csum[2 * g + 1] = 0.0;
-    q.ccnt[2 * g + 0] = 0;
-    q.ccnt[2 * g + 1] = 0;
+// Column-wise centre from the column's sum and count.
+__device__ __forceinline__ float col_centre(const QuantArgs& q, uint32_t g) {
+    const uint32_t n = q.ccnt[g];
+    return n ? (float)(q.csum[g] / (double)n) : 0.0f;
 }
 
+template <bool COLUMN>
 __global__ __launch_bounds__(kBlock) void k_quant(QuantArgs q) {
     const uint64_t j = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint64_t total = q.qbase[q.T];  // entries sent (the grid covers k_total >= total)
+    // column-wise centres are given out here, and each entry forms its own
+    if (COLUMN && j < q.groups) {
+        q.means[2 * j + 0] = col_centre(q, 2 * (uint32_t)j);
+        q.means[2 * j + 1] = col_centre(q, 2 * (uint32_t)j + 1);
+    }
+    // entries sent (the grid covers k_total >= total; the first slots are not formed where that is 0)
+    const uint64_t total = !COLUMN || q.k_total ? q.qbase[q.T] : 0u;
     const bool valid = j < total;
     bool neg = false;
     if (valid) {
@@ -330,8 +368,9 @@ __global__ __launch_bounds__(kBlock) void k_quant(QuantArgs q) {
         const float x = q.val[j];
         neg = x < 0.0f;
         const uint32_t i = q.idx[j];
-        const uint32_t g = q.qkind == kQuantColumnMean ? q.colbase[lo] + (i - q.tensor_off[lo]) % q.columns[lo] : lo;
-        const float centre = neg ? q.means[2 * g + 1] : q.means[2 * g + 0];
+        const float centre = COLUMN ? col_centre(q, 2 * (q.colbase[lo] + (i - q.tensor_off[lo]) % q.columns[lo]) + (neg ? 1u : 0u))
+                             : neg  ? q.means[2 * lo + 1]
+                                    : q.means[2 * lo + 0];
         if (i < q.N) q.res[i] = x - centre;
     }
     const uint64_t m = ballot(valid && neg);
@@ -344,26 +383,39 @@ __global__ __launch_bounds__(kBlock) void k_quant(QuantArgs q) {
 static inline uint32_t blocks_for_waves(uint32_t waves) { return (waves + kWavesPerBlock - 1) / kWavesPerBlock; }
 
 hipError_t launch_quant(const QuantArgs& q, hipStream_t st) {
-    if (q.direct) {
+    const bool column = q.qkind == kQuantColumnMean;
+    const bool local = column && q.T <= kColLocalT;  // k_colsum finds the first slots itself
+    if (!local && q.direct) {
         const bool sums = q.qkind == kQuantSignMean || q.qkind == kQuantGlobalMean;
         const bool sliced = sums && q.k_total > kMeansDirectK, base = sliced || q.T > kMeansLocalT;
         if (base) hipLaunchKernelGGL(k_qbase, dim3(1), dim3(kMeansThreads), 0, st, q);
         if (sliced) hipLaunchKernelGGL(k_qsum, dim3((uint32_t)((q.k_total + kQSlice - 1) / kQSlice)), dim3(kBlock), 0, st, q);
         // (column means need the first slots only, of one block)
-        hipLaunchKernelGGL(k_dmeans, dim3(q.qkind == kQuantColumnMean ? 1u : q.T), dim3(kMeansThreads), 0, st, q,
-                           sliced ? 1u : 0u, base ? 1u : 0u);
-    } else {
+        if (!column || !base)
+            hipLaunchKernelGGL(k_dmeans, dim3(column ? 1u : q.T), dim3(kMeansThreads), 0, st, q, sliced ? 1u : 0u,
+                               base ? 1u : 0u);
+    } else if (!local) {
         hipLaunchKernelGGL(k_means, dim3(blocks_for_waves(q.T)), dim3(kBlock), 0, st, q);
     }
-    if (q.qkind == kQuantColumnMean && q.groups > 0) {
-        if (q.k_total > 0)
-            hipLaunchKernelGGL(k_colsum, dim3((uint32_t)((q.k_total + kColSlice - 1) / kColSlice)), dim3(kBlock), 0, st,
-                               q);
-        hipLaunchKernelGGL(k_colmeans, dim3((q.groups + kBlock - 1) / kBlock), dim3(kBlock), 0, st, q);
+    if (column && q.k_total > 0) {
+        // Short slices fill the device from few entries; of many, long ones save
+        // adds to columns that many blocks share (a call with slices of 1,024 /
+        // 2,048 / 4,096 in us: 120,000 entries over 200 columns x 6 tensors 94 /
+        // 96 / 100; 21,000 ragged ones 100 / 103 / 111, of 256 98; 960,000 over 8
+        // 132 / 126 / 124; 4.25M over 500 381 / 336 / 322).
+        const uint32_t per = q.k_total <= kColTinyK ? 1u : q.k_total <= kColSmallK ? 4u : q.k_total <= kColMidK ? 8u : 16u;
+        const uint32_t slice = per * kBlock;
+        const dim3 g((uint32_t)((q.k_total + slice - 1) / slice));
+        if (per == 1) hipLaunchKernelGGL(k_colsum<1>, g, dim3(kBlock), 0, st, q, local ? 0u : 1u);
+        else if (per == 4) hipLaunchKernelGGL(k_colsum<4>, g, dim3(kBlock), 0, st, q, local ? 0u : 1u);
+        else if (per == 8) hipLaunchKernelGGL(k_colsum<8>, g, dim3(kBlock), 0, st, q, local ? 0u : 1u);
+        else hipLaunchKernelGGL(k_colsum<16>, g, dim3(kBlock), 0, st, q, local ? 0u : 1u);
     }
-    if (q.k_total > 0) {
-        const uint64_t blocks = (q.k_total + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(k_quant, dim3((uint32_t)blocks), dim3(kBlock), 0, st, q);
+    const uint64_t items = std::max<uint64_t>(q.k_total, column ? q.groups : 0u);
+    if (items > 0) {
+        const dim3 g((uint32_t)((items + kBlock - 1) / kBlock));
+        if (column) hipLaunchKernelGGL(k_quant<true>, g, dim3(kBlock), 0, st, q);
+        else hipLaunchKernelGGL(k_quant<false>, g, dim3(kBlock), 0, st, q);
     }
     return hipGetLastError();
 }
