@@ -27,7 +27,7 @@ constexpr uint64_t kStaticMaxN = 1ull << 21;  // elements of the layout (2,097,1
 constexpr uint32_t kStaticMaxT = 64;          // tensors of the layout
 constexpr size_t kStaticBytes = 24ull << 20;  // the scratch array: 24 MiB per GPU
 constexpr int kStaticMaxDevices = 64;
-static_assert(kStaticMaxN <= (uint64_t)kDirectMaxUnits * kUnitLen, "only the direct form's scratch is laid out here");
+static_assert(kStaticMaxN <= (uint64_t)kDirectMaxUnits * kUnitLen, "only the direct form's buffers are laid out here");
 
 // Every gd_compress_static call on a device shares that device's copy.
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
