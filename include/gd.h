@@ -235,9 +235,12 @@ gd_status gd_compress_sampled(gd_ctx* ctx, const float* grad, const float* base,
  *   pushes to a 37M shard).  The library keeps one such table per device and
  *   stream (per host thread for the per-thread default stream) and reuses it
  *   on later calls on that stream; it is allocated with hipMalloc on the
- *   first call that needs it (or a larger one) and kept until the process
- *   ends, so make the first call on a stream outside graph capture (a captured
- *   call of more than 8 pushes needs no table).  If that allocation fails the
+ *   first call that needs it, so make the first call on a stream outside graph
+ *   capture (a captured call of more than 8 pushes needs no table).  A call that
+ *   needs a larger one gets a new table, of at least twice the size.  Every table
+ *   is kept until the process ends, so that a captured call may be replayed at
+ *   any time; a replay must not overlap in time with other applies on the stream
+ *   it was captured on, whose table it shares.  If that allocation fails the
  *   pushes are applied in the other form; the results are the same.
  *   The result is deterministic when the precondition above holds.  It is not
  *   checked on the device (that would need a host synchronisation): an index

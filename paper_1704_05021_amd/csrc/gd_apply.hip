@@ -451,9 +451,11 @@ static std::atomic<int> g_apply_form{0};
 // ordering the calls of all streams on one table, each cost about 5-6 us per
 // call.)  The per-thread default stream is one stream per host thread, so
 // its tables are kept per thread.  The mutex also keeps the two launches of
-// one call together when host threads share a stream.  A table grows when a
-// call needs more (hipFree of the old one waits for the device) and is kept
-// until the process ends.
+// one call together when host threads share a stream.  A call that needs more
+// than its stream's table gets a new one of at least twice the size.  No table
+// is ever freed: a captured call holds its address for every replay of its
+// graph, and nothing tells when the last replay was.  So all tables of a stream
+// take less than twice the largest, itself below twice what a call needed.
 struct TableKey {
     int dev;
     uintptr_t stream;
@@ -475,11 +477,14 @@ static uint32_t* stream_table(hipStream_t st, size_t bytes) {
     const TableKey key{dev, reinterpret_cast<uintptr_t>(st), st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()};
     auto& slot = g_tables[key];
     if (slot.second < bytes) {
-        if (slot.first) (void)hipFree(slot.first);
-        slot = {nullptr, 0};
-        const size_t want = (bytes + 65535u) & ~(size_t)65535u;
+        const size_t least = (bytes + 65535u) & ~(size_t)65535u;
+        size_t want = std::max(least, 2 * slot.second);
         void* q = nullptr;
-        if (hipMalloc(&q, want) != hipSuccess) return nullptr;
+        if (hipMalloc(&q, want) != hipSuccess) {
+            (void)hipGetLastError();
+            want = least;
+            if (hipMalloc(&q, want) != hipSuccess) return nullptr;
+        }
         slot = {q, want};
     }
     return static_cast<uint32_t*>(slot.first);

@@ -85,3 +85,38 @@ def test_captured_many_clients():
         q = torch.from_numpy(want).cuda()
         gd.apply_sparse(q, ti, tv, 0.3)  # eager work between the replays
         _same(q, oracle.apply_sparse(want, idx, val, 0.3))
+
+
+def test_captured_table_outlives_larger_calls():
+    # 64 clients need a larger bounds table than the captured call's stream had
+    # (17,216 words past the 16,384 of the least table): the replays still use theirs
+    rng = np.random.default_rng(4)
+    n = 1_100_001
+
+    def on_gpu(clients, density):
+        idx, val = _pushes(rng, n, clients, density, 100)
+        return idx, val, [torch.from_numpy(i.view(np.int32)).cuda() for i in idx], [torch.from_numpy(v).cuda() for v in val]
+
+    few, many = on_gpu(4, 1 / 8), on_gpu(64, 1 / 4)
+    p0 = rng.normal(0, 1, n).astype(np.float32)
+    p = torch.from_numpy(p0).cuda()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        gd.apply_sparse(p, few[2], few[3], 0.0)  # the stream's first call makes its table
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        gd.apply_sparse(p, few[2], few[3], 0.3)
+    want = p0
+    for _ in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        want = oracle.apply_sparse(want, few[0], few[1], 0.3)
+        _same(p, want)
+        q = torch.from_numpy(want).cuda()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            gd.apply_sparse(q, many[2], many[3], 0.3)  # eager work between the replays
+        stream.synchronize()
+        _same(q, oracle.apply_sparse(want, many[0], many[1], 0.3))
