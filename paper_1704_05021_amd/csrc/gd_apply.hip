@@ -469,6 +469,17 @@ struct TableKey {
 static std::mutex g_tab_mu;
 static std::map<TableKey, std::pair<void*, size_t>> g_tables;
 
+// hipMalloc by a thread in the relaxed capture mode: in the default mode it is
+// refused while any stream in the process is being captured, and breaks that
+// capture (of another program part, perhaps, that this call has nothing to do with).
+static hipError_t malloc_beside_captures(void** p, size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return hipMalloc(p, bytes);
+    const hipError_t e = hipMalloc(p, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return e;
+}
+
 // The table of the current device and stream st, at least `bytes` long, or
 // null if it cannot be allocated.  Called with g_tab_mu held.
 static uint32_t* stream_table(hipStream_t st, size_t bytes) {
@@ -480,10 +491,10 @@ static uint32_t* stream_table(hipStream_t st, size_t bytes) {
         const size_t least = (bytes + 65535u) & ~(size_t)65535u;
         size_t want = std::max(least, 2 * slot.second);
         void* q = nullptr;
-        if (hipMalloc(&q, want) != hipSuccess) {
+        if (malloc_beside_captures(&q, want) != hipSuccess) {
             (void)hipGetLastError();
             want = least;
-            if (hipMalloc(&q, want) != hipSuccess) return nullptr;
+            if (malloc_beside_captures(&q, want) != hipSuccess) return nullptr;
         }
         slot = {q, want};
     }

@@ -23,3 +23,15 @@ for n in range(2_000_000, 4_000_000_000, 50_000_000):
     assert apply(n, 64, n // 8, 32) == 2
 assert get("g_frees") == 0 and get("g_allocs") - before < 24
 """, tmp_path)
+
+
+def test_a_table_may_be_made_while_another_stream_is_captured(tmp_path):
+    # in the default capture mode, an allocation by a thread in the same mode is
+    # refused and breaks the capture, whatever stream it is for
+    hip_stub.run("""
+put("g_other_capture", 1)
+for clients in (4, 12, 64):
+    assert apply(37_000_000, clients, 1_000_000) == 2
+    assert get("g_refused") == 0, clients
+    assert get("g_mode") == 0              # and the thread's own mode is as before
+""", tmp_path)

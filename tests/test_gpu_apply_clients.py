@@ -120,3 +120,32 @@ def test_captured_table_outlives_larger_calls():
             gd.apply_sparse(q, many[2], many[3], 0.3)  # eager work between the replays
         stream.synchronize()
         _same(q, oracle.apply_sparse(want, many[0], many[1], 0.3))
+
+
+@pytest.mark.parametrize("clients", [4, 12])
+def test_first_call_beside_a_capture(clients):
+    # a first call on one stream makes its bounds table while another stream is
+    # being captured: the capture goes on, and both results are right
+    rng = np.random.default_rng(clients)
+    n = 90_001
+    idx, val = _pushes(rng, n, clients, 1 / 4, 100)
+    ti, tv = [torch.from_numpy(i.view(np.int32)).cuda() for i in idx], [torch.from_numpy(v).cuda() for v in val]
+    p0 = rng.normal(0, 1, n).astype(np.float32)
+    p, q = torch.from_numpy(p0).cuda(), torch.from_numpy(p0).cuda()
+    captured, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=captured):
+        p.mul_(2.0)
+        gd.apply_sparse(q, ti, tv, 0.3, stream=other)
+        p.add_(1.0)
+    torch.cuda.synchronize()
+    _same(q, oracle.apply_sparse(p0, idx, val, 0.3))
+    want = p0
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        want = (want * np.float32(2.0) + np.float32(1.0)).astype(np.float32)
+        _same(p, want)
+        gd.apply_sparse(q, ti, tv, 0.3, stream=other)
+        torch.cuda.synchronize()
