@@ -337,10 +337,10 @@ gd_status gd_debug_force_bracket(gd_ctx* ctx, int mode);
  * in this process, so that tests can run both forms at any density.  The
  * results do not change; only the work done does.  form 0: chosen per call
  * (streaming, which reads the whole shard in order, when params is 16-byte
- * aligned and the pushes hold at least one entry per 24 to 128 parameters, by
- * the size of the shard and the number of pushes, and the call is not a
- * captured one of more than 8 pushes; else scattered, which reads only the
- * pushed parameters); 1: scattered; 2: streaming wherever params is 16-byte
+ * aligned and the pushes hold at least one entry per 64 parameters, or of more
+ * than 8 pushes one per 128 (per 48 on shards of more than 2^24 parameters), and
+ * the call is not a captured one of more than 8 pushes; else scattered, which
+ * reads only the pushed parameters); 1: scattered; 2: streaming wherever params is 16-byte
  * aligned.  A process-wide setting: it applies to every device and thread.
  * GD_ERR_ARG for other forms.
  */

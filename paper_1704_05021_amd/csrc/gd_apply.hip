@@ -509,19 +509,23 @@ hipError_t launch_apply(const ApplyArgs& a, uint32_t max_nnz, hipStream_t st) {
     for (uint32_t c = 0; c < a.C; ++c) total += a.nnz[c];
     // Streaming reads every line of the shard, in order; scattered reads and
     // writes words, and searches for the indices that several clients hold.
-    // The line lies where the two measure alike, over indices spread evenly
-    // and over indices in a sixteenth of the rows of 1,000 (in this order, us
-    // scattered / streaming).  One client: 9.7M parameters, an entry per 32:
-    // 13.0 / 16.3 and 10.8 / 13.4, per 16: 15.6 / 18.4; 37M, per 32: 40 / 57 and
-    // 20 / 37, per 16: 72 / 68.  Four: 9.7M, per 64: 15.4 / 17.7 and 16.1 / 14.4,
-    // per 32: 17.3 / 18.3 and 54.9 / 16.2; 37M, per 64: 28 / 45 and 21 / 37, per
-    // 32: 47 / 58 and 76 / 40.  Sixteen: 9.7M, per 256: 19.9 / 24.1 and 22.9 /
-    // 22.4, per 64: 27.6 / 25.1 and 35.9 / 22.5; 37M, per 64: 38 / 56 and 42 / 43,
-    // per 32: 66 / 63 and 225 / 49.
+    // How the pushes lie is not known here.  Spread evenly they cost scattered
+    // less up to about an entry per 32 parameters, but where most lie in few
+    // rows (a vocabulary sorted by frequency) a bucket overflows the staged
+    // entries and its block reads the lists in place, while streaming depends
+    // little on it.  us, scattered / streaming, evenly and all in the shard's
+    // first rows: 37M parameters, an entry per 60: 1 client 24 / 35 and 39 / 30,
+    // 4 clients 29 / 38 and 1204 / 79, 8 clients 35 / 45 and 3432 / 172.  So the
+    // line of up to 8 clients is where about 40% of the shard's lines hold an
+    // entry if they lie evenly: 12 us lost at most there, against 3 ms.
+    // With more clients streaming costs a turn of barriers more for each, and
+    // evenly the two measure alike at the lines below (16 clients: 9.7M, per 100:
+    // 25 / 29, per 50: 28 / 28; 37M, per 50: 50 / 57, per 30: 82 / 59; in the first
+    // rows 9.7M, per 100: 3157 / 487; 37M, per 30: 3942 / 500).
     const int form = g_apply_form.load();
     const bool aligned = (reinterpret_cast<uintptr_t>(a.p) & 15u) == 0;
     const bool cached = a.n <= (1u << 24);  // the shard stays in the caches (64 MiB)
-    const uint64_t sparse = a.C == 1u ? 24u : !cached ? 48u : a.C <= 8u ? 64u : 128u;
+    const uint64_t sparse = a.C <= 8u ? 64u : cached ? 128u : 48u;
     bool stream = aligned && form != 1 && (form == 2 || total * sparse >= a.n);
     if (stream && form != 2 && a.C > 8u) {
         // A captured call of more than 8 clients is scattered, so that no
