@@ -103,9 +103,8 @@ struct SegState {
     uint32_t zero;  // 1 when fewer than k keys are nonzero and all of them are candidates: T = 0
     uint32_t runs;  // kept between calls: 1 when the last sample's units counted like independent
                     // draws, so the next call samples one run of 16 neighbours per unit
-    uint32_t blo;   // direct form: the keys [blo, blo + 2^bbits) that hold the threshold key
-    uint32_t bbits;
-    uint32_t pad[2];
+    uint32_t blo;   // direct form: first of the 512 keys that hold the threshold key (zero mode: 0)
+    uint32_t pad[3];
 };
 
 __device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }

@@ -35,8 +35,9 @@
 
 namespace gd {
 
-constexpr uint32_t kFewBits = 9;               // a bin of at most this many low key bits ...
-constexpr uint32_t kDenseKeys = 1u << kFewBits;  // ... whose piece holds more keys than this stores counts
+constexpr uint32_t kFewBits = 9;                 // low key bits below the prefix that two digits leave
+constexpr uint32_t kBinKeys = 1u << kFewBits;    // keys of such a bin
+constexpr uint32_t kListKeys = 16;               // a piece with more different keys in the bin stores counts
 constexpr uint32_t kDenseFlag = 0x80000000u;     // in PieceInfo::in: suffix counts stored in place of keys
 
 struct Piece {
@@ -221,21 +222,34 @@ struct Resolved {
     uint32_t equal;  // keys equal to T there
 };
 
-// Keys above and equal to thr among the bin's keys of one piece.
+// What a piece leaves of its keys in the bin: nothing, one value (`in` times),
+// a list of `in` keys, or (kDenseFlag) the number of its keys at or above each
+// of the bin's values.  Lists are short but for the segment's first and last
+// piece, which may be too short to store counts.
+__device__ __forceinline__ bool one_key(const PieceInfo& p) { return p.kmin == p.kmax; }
+__device__ __forceinline__ bool long_list(const PieceInfo& p) {
+    return !(p.in & kDenseFlag) && p.in > kListKeys && !one_key(p);
+}
+// Keys at or above bin value x (0 to kBinKeys) of a piece that stores counts.
+__device__ __forceinline__ uint32_t dense_ge(const DirectArgs& a, uint32_t at, uint32_t x) {
+    return x < kBinKeys ? a.ent[at + x] : 0u;
+}
+
+// Keys above and equal to thr among the bin's keys of one piece (a long list's
+// not counted).
 __device__ __forceinline__ void count_piece(const DirectArgs& a, const PieceInfo& p, uint32_t at, uint32_t lo, uint32_t thr,
                                             uint32_t& g, uint32_t& e) {
     const uint32_t n = p.in & ~kDenseFlag;
     if (n == 0 || p.kmax < thr) return;
     if (p.kmin > thr) {
         g += n;
-    } else if (p.kmin == p.kmax) {
+    } else if (one_key(p)) {
         e += n;
     } else if (p.in & kDenseFlag) {
-        const uint32_t x = thr - lo;  // counts of keys at or above each low value
-        const uint32_t ge = a.ent[at + x], gt = x + 1 < kDenseKeys ? a.ent[at + x + 1] : 0u;
+        const uint32_t ge = dense_ge(a, at, thr - lo), gt = dense_ge(a, at, thr - lo + 1);
         g += gt;
         e += ge - gt;
-    } else {
+    } else if (!long_list(p)) {
         for (uint32_t i = 0; i < n; ++i) {
             const uint32_t k = a.ent[at + i];
             g += k > thr;
@@ -248,106 +262,144 @@ __device__ __forceinline__ void count_piece(const DirectArgs& a, const PieceInfo
 // r-th largest of them) from the pieces' records, and counts the keys above
 // and equal to it in the pieces before `pair`.  Called by the whole block;
 // h is a kSelBins-word LDS histogram.
+//
+// Every emitting block does this, so its work is bounded whatever the values: a
+// thread reads the records of P / NT pieces (P at most 1,152), a list of at most
+// kListKeys keys for each, and where pieces store counts one of them for each
+// step of a search over the bin's nine bits.  (Adding up all counts of all
+// pieces in every block took 1,735 us a call at 4.7M elements within 4,096
+// neighbouring values, the candidate form 1,009; now 110.)
 template <int NT>
 __device__ Resolved resolve(const DirectArgs& a, uint32_t s, uint32_t sa, uint32_t sb, uint32_t pair, uint32_t lo,
-                            uint32_t bits, uint32_t r, uint32_t* h, uint32_t* lds) {
+                            uint32_t r, uint32_t* h, uint32_t* lds) {
     const int tid = threadIdx.x;
     const uint32_t j0 = chunk_of(a, sa) + s, j1 = chunk_of(a, sb - 1) + s + 1;
-    uint32_t above = 0, kmin = kNoKey, kmax = 0, dense = 0;
+    uint32_t above = 0, kmin = kNoKey, kmax = 0, forms = 0;  // forms: 1, some piece stores counts; 2, a long list
     for (uint32_t j = j0 + tid; j < j1; j += NT) {
         const PieceInfo p = a.info[j];
         if (j < pair) above += p.gt;
         if (p.in) {
             kmin = min(kmin, p.kmin);
             kmax = max(kmax, p.kmax);
-            dense |= p.in >> 31;
+            forms |= (p.in >> 31) | (long_list(p) ? 2u : 0u);
         }
     }
     // sums and extremes over the block
     uint32_t* red = lds;  // [NT / 64][4]
     {
         const uint32_t x0 = wave_sum(above), x1 = wave_min(kmin), x2 = lane_value(wave_incl_max(kmax), kWave - 1);
-        const uint64_t m = ballot(dense != 0);
+        const uint64_t m1 = ballot((forms & 1u) != 0), m2 = ballot((forms & 2u) != 0);
         if (lane_id() == 0) {
             uint32_t* q = red + 4 * (threadIdx.x / kWave);
             q[0] = x0;
             q[1] = x1;
             q[2] = x2;
-            q[3] = m != 0;
+            q[3] = (m1 != 0 ? 1u : 0u) | (m2 != 0 ? 2u : 0u);
         }
         __syncthreads();
-        above = 0, kmin = kNoKey, kmax = 0, dense = 0;
+        above = 0, kmin = kNoKey, kmax = 0, forms = 0;
         for (int i = 0; i < NT / kWave; ++i) {
             above += red[4 * i];
             kmin = min(kmin, red[4 * i + 1]);
             kmax = max(kmax, red[4 * i + 2]);
-            dense |= red[4 * i + 3];
+            forms |= red[4 * i + 3];
         }
         __syncthreads();
         above = __builtin_amdgcn_readfirstlane(above);
         kmin = __builtin_amdgcn_readfirstlane(kmin);
         kmax = __builtin_amdgcn_readfirstlane(kmax);
-        dense = __builtin_amdgcn_readfirstlane(dense);
+        forms = __builtin_amdgcn_readfirstlane(forms);
     }
-    Resolved z{lo, r, above, 0u};
-    if (kmin >= kmax) {  // one key (or, in the zero mode of the candidate form, none here)
-        z.thr = kmin == kNoKey ? lo : kmin;
-    } else {
-        uint32_t base = lo, rem = bits, rank = r;
-        while (rem > 0) {
-            const uint32_t nb = rem < 11u ? rem : 11u, sh = rem - nb;
-            clear_hist<NT>(h);
-            for (uint32_t j = j0 + tid; j < j1; j += NT) {
-                const PieceInfo p = a.info[j];
-                if (p.in == 0 || p.kmax < base || (p.kmin > base && p.kmin - base >= (1u << rem))) continue;
-                if (p.kmin == p.kmax) {
-                    atomicAdd(&h[(p.kmin - base) >> sh], p.in);
-                } else if (!(p.in & kDenseFlag)) {
-                    const uint32_t at = piece_start(a, s, sa, j);
-                    for (uint32_t i = 0; i < p.in; ++i) {
-                        const uint32_t d = a.ent[at + i] - base;
-                        if (d < (1u << rem)) atomicAdd(&h[d >> sh], 1u);
-                    }
-                }
-            }
-            if (dense) {  // (only where bits <= kFewBits: one level, base == lo)
-                for (uint32_t j = j0; j < j1; ++j) {
-                    const PieceInfo p = a.info[j];
-                    if (!(p.in & kDenseFlag) || p.kmin == p.kmax) continue;
-                    const uint32_t at = piece_start(a, s, sa, j);
-                    for (uint32_t x = tid; x < (1u << bits); x += NT) {
-                        const uint32_t ge = a.ent[at + x], gt = x + 1 < kDenseKeys ? a.ent[at + x + 1] : 0u;
-                        if (ge != gt) atomicAdd(&h[x], ge - gt);
-                    }
-                }
-            }
-            __syncthreads();
-            uint32_t d, ab;
-            block_pick<NT, kSelBins, 1>(h, rank, lds, d, ab);
-            base += d << sh;
-            rank -= ab;
-            rem = sh;
+    // sums over the block, in every thread (waits at both ends)
+    const auto block_sums = [&](uint32_t& u, uint32_t& v) {
+        u = wave_sum(u);
+        v = wave_sum(v);
+        if (lane_id() == 0) {
+            red[2 * (threadIdx.x / kWave)] = u;
+            red[2 * (threadIdx.x / kWave) + 1] = v;
         }
-        z.thr = base;
-        z.need = rank;
+        __syncthreads();
+        u = v = 0;
+        for (int i = 0; i < NT / kWave; ++i) {
+            u += red[2 * i];
+            v += red[2 * i + 1];
+        }
+        __syncthreads();
+        u = __builtin_amdgcn_readfirstlane(u);
+        v = __builtin_amdgcn_readfirstlane(v);
+    };
+    Resolved z{kmin, r, above, 0u};
+    if (kmin < kmax) {  // (one key in the whole bin is the threshold)
+        // the keys that are listed, by value
+        clear_hist<NT, (int)kBinKeys>(h);
+        for (uint32_t j = j0 + tid; j < j1; j += NT) {
+            const PieceInfo p = a.info[j];
+            if (p.in == 0) continue;
+            if (one_key(p)) {
+                atomicAdd(&h[p.kmin - lo], p.in);
+            } else if (!(p.in & kDenseFlag) && !long_list(p)) {
+                const uint32_t at = piece_start(a, s, sa, j);
+                for (uint32_t i = 0; i < p.in; ++i) atomicAdd(&h[a.ent[at + i] - lo], 1u);
+            }
+        }
+        // the first and the last piece
+        for (uint32_t j = j0; j < j1 && (forms & 2u); j += max(j1 - 1 - j0, 1u)) {
+            const PieceInfo p = a.info[j];
+            const uint32_t at = piece_start(a, s, sa, j);
+            for (uint32_t i = tid; long_list(p) && i < p.in; i += NT) atomicAdd(&h[a.ent[at + i] - lo], 1u);
+        }
+        __syncthreads();
+        uint32_t d, ab;
+        if (!(forms & 1u)) {
+            block_pick<NT, (int)kBinKeys, 1>(h, r, lds, d, ab);
+        } else {
+            // h[x] = listed keys at or above x; then the largest x with at least r keys at or above it
+            static_assert(kBinKeys == 2 * NT, "two values per thread");
+            const int top = (int)kBinKeys - 2 * tid;
+            const uint32_t c1 = h[top - 1], c0 = h[top - 2];
+            uint32_t total;
+            const uint32_t excl = block_excl_scan<NT>(c0 + c1, lds, &total);
+            h[top - 1] = excl + c1;
+            h[top - 2] = excl + c1 + c0;
+            __syncthreads();
+            d = 0, ab = 0;
+            uint32_t end = kBinKeys;  // fewer than r keys at or above it: ab
+            while (end - d > 1) {
+                const uint32_t mid = (d + end) >> 1;
+                uint32_t c = 0, none = 0;
+                for (uint32_t j = j0 + tid; j < j1; j += NT) {
+                    const PieceInfo p = a.info[j];
+                    if (p.in & kDenseFlag) c += dense_ge(a, piece_start(a, s, sa, j), mid);
+                }
+                block_sums(c, none);
+                c += h[mid];
+                if (c >= r) {
+                    d = mid;
+                } else {
+                    end = mid;
+                    ab = c;
+                }
+            }
+        }
+        z.thr = lo + d;
+        z.need = r - ab;
     }
     uint32_t g = 0, e = 0;
     for (uint32_t j = j0 + tid; j < pair; j += NT) count_piece(a, a.info[j], piece_start(a, s, sa, j), lo, z.thr, g, e);
-    g = wave_sum(g);
-    e = wave_sum(e);
-    if (lane_id() == 0) {
-        red[2 * (threadIdx.x / kWave)] = g;
-        red[2 * (threadIdx.x / kWave) + 1] = e;
+    if ((forms & 2u) && j0 < pair) {  // (the last piece is not before another)
+        const PieceInfo p = a.info[j0];
+        for (uint32_t i = tid; long_list(p) && i < p.in; i += NT) {
+            const uint32_t k = a.ent[sa + i];
+            // as count_piece: a list all above or below the threshold is counted there
+            if (p.kmin <= z.thr && z.thr <= p.kmax) {
+                g += k > z.thr;
+                e += k == z.thr;
+            }
+        }
     }
-    __syncthreads();
-    g = e = 0;
-    for (int i = 0; i < NT / kWave; ++i) {
-        g += red[2 * i];
-        e += red[2 * i + 1];
-    }
-    __syncthreads();
-    z.above += __builtin_amdgcn_readfirstlane(g);
-    z.equal = __builtin_amdgcn_readfirstlane(e);
+    block_sums(g, e);
+    z.above += g;
+    z.equal = e;
     return z;
 }
 template <int NT>
@@ -486,7 +538,7 @@ __device__ __forceinline__ void direct_collect(const DirectArgs& a, uint32_t* h,
         r = g.r1 - above;
     }
     if (tid < 4) sum[tid] = tid == 2 ? kNoKey : 0u;
-    for (uint32_t i = tid; i < kDenseKeys; i += NT) h[i] = 0;
+    for (uint32_t i = tid; i < kBinKeys; i += NT) h[i] = 0;
     __syncthreads();
     uint32_t gt = 0, nz = 0, kmin = kNoKey, kmax = 0;
     for_keys<UPW>(a, c, p, x, [&](uint32_t key, uint32_t, bool in) {
@@ -516,15 +568,15 @@ __device__ __forceinline__ void direct_collect(const DirectArgs& a, uint32_t* h,
         }
     }
     __syncthreads();
-    // a piece with many different keys in the bin stores, in place of the
-    // keys, how many are at or above each of its 512 values
-    const bool dense = bits != 0 && sum[1] > kDenseKeys && sum[2] != sum[3];
+    // a piece with many different keys in the bin stores, in place of the keys,
+    // how many are at or above each of its 512 values, if it has room for them
+    // (every piece but a segment's first and last does: those are whole chunks)
+    const bool dense = bits != 0 && sum[1] > kListKeys && sum[2] != sum[3] && p.eb - p.ea >= kBinKeys;
     if (dense && tid < kWave) {
         uint32_t carry = 0;
-        for (int i = kDenseKeys / kWave; i-- > 0;) {
-            const uint32_t v = h[kDenseKeys - 1 - (kDenseKeys / kWave - 1 - i) * kWave - tid];
-            const uint32_t incl = wave_incl_scan(v) + carry;
-            a.ent[p.ea + kDenseKeys - 1 - (kDenseKeys / kWave - 1 - i) * kWave - tid] = incl;
+        for (uint32_t x = kBinKeys - 1 - tid; x < kBinKeys; x -= kWave) {  // (wraps past 0 at the end)
+            const uint32_t incl = wave_incl_scan(h[x]) + carry;
+            a.ent[p.ea + x] = incl;
             carry = lane_value(incl, kWave - 1);
         }
     }
@@ -533,7 +585,6 @@ __device__ __forceinline__ void direct_collect(const DirectArgs& a, uint32_t* h,
         if (p.ea == p.sa) {
             SegState& o = a.seg[p.s];
             o.blo = lo;
-            o.bbits = bits;
             o.r2 = r;
         }
     }
@@ -554,7 +605,7 @@ __device__ __forceinline__ void direct_emit(const DirectArgs& a, uint32_t* h, ui
     const uint32_t k = keep_of(p.sb - p.sa, a.keep_ppm);
     if (k == 0) return;
     const SegState g = a.seg[p.s];
-    const Resolved z = resolve<NT>(a, p.s, p.sa, p.sb, blockIdx.x, g.blo, g.bbits, g.r2, h, lds);
+    const Resolved z = resolve<NT>(a, p.s, p.sa, p.sb, blockIdx.x, g.blo, g.r2, h, lds);
     if (p.ea == p.sa && threadIdx.x == 0) {
         a.seg[p.s].thr = z.thr;
         a.seg[p.s].need = z.need;
@@ -718,7 +769,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_dhist(DirectArgs a) {
 
 template <int UPW, bool PULL>
 __global__ __launch_bounds__(kDirectThreads) void k_dcollect(DirectArgs a) {
-    __shared__ __align__(16) uint32_t h[kDenseKeys];
+    __shared__ __align__(16) uint32_t h[kBinKeys];
     __shared__ __align__(16) uint32_t lds[kPickLds<kDirectThreads>];
     {  // the first digit's histograms, for the next call
         const size_t words = (size_t)a.S * a.copies * (kSelBins / 4);

@@ -50,6 +50,23 @@ def test_many_keys_in_one_prefix(per_tensor, spread):
                        debug_bracket=debug, what=f"spread={spread} drop={drop} debug={debug}")
 
 
+@pytest.mark.parametrize("spread", [17, 512, 512 * 40, 512 * 256, 512 * 600], ids=lambda s: f"{s}_values")
+def test_lists_and_counts_of_keys(spread):
+    # keys in the threshold's prefix per piece of 4,096 elements: all of them (counts
+    # are stored), about 100 (counts), 16 (counts in some pieces, lists in others) and 7
+    # (lists); segments that begin and end with pieces of 196 and 312 elements, too
+    # short for counts, of one such piece, and of many pieces
+    rng = np.random.default_rng(spread)
+    off = [0, 3_900, 12_600, 12_700, 700_001]
+    n = off[-1]
+    g = (np.float32(1.0).view(np.uint32) + rng.integers(0, spread, n).astype(np.uint32)).view(np.float32)
+    g = g * np.where(rng.random(n) < 0.5, -1, 1).astype(np.float32)
+    comp = gd.Compressor(off)
+    for per in (False, True):
+        for drop in (0.99, 0.7, 0.3):
+            check_case(g, np.zeros(n, np.float32), off, drop, per, False, comp=comp, what=f"spread={spread} per={per} drop={drop}")
+
+
 @pytest.mark.parametrize("quant", [gd.GD_QUANT_SIGN_MEAN, gd.GD_QUANT_GLOBAL_MEAN], ids=["sign_mean", "global_mean"])
 @pytest.mark.parametrize("keep", [65_536, 65_537])
 def test_sums_by_slices(quant, keep):
