@@ -152,43 +152,123 @@ __device__ __forceinline__ void add_value(double v[4], float x) {
     }
 }
 
+// The last t in [0, n) with base(t) <= j, of a nondecreasing base with base(0) <= j:
+// 64 probes a round.  All lanes of the wave call it.
+template <typename Base>
+__device__ __forceinline__ uint32_t wave_last_at_most(const Base& base, uint32_t n, uint32_t j) {
+    uint32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave;
+        const uint64_t p = lo + (uint64_t)lane_id() * step;
+        // probes rise with the lane, so those at most j form a prefix; lane 0's is one
+        lo += (popc64(ballot(p < hi && base((uint32_t)p) <= j)) - 1u) * step;
+        hi = hi - lo > step ? lo + step : hi;
+    }
+    return lo;
+}
+
 // Sums of every slice of kQSlice sent entries: per tensor under the sign mean
 // (slice j and tensor t have record j + t: along the list either grows from
 // one pair to the next, so a tensor's records are consecutive), else over all.
+// A slice inside one tensor is summed by the block.  Else the slice is staged
+// in LDS and its tensors are dealt out, those of at most kQThreadSum entries to
+// threads and the others, at most 124, to waves: a slice may hold thousands of
+// tensors, and summing each with the block waited at four barriers a tensor
+// (100,000 entries of 3,000 tensors: 249 us a call, the candidate form 110; now 67).
+constexpr uint32_t kQThreadSum = 32;
+
 __global__ __launch_bounds__(kBlock) void k_qsum(QuantArgs q) {
     __shared__ double lds[4 * kWavesPerBlock];
+    __shared__ float xs[kQSlice];
+    __shared__ uint32_t more[kQSlice / (kQThreadSum + 1) + 1], nmore;
     const int tid = threadIdx.x;
     constexpr int PER = kQSlice / kBlock;
     const uint64_t j0 = (uint64_t)blockIdx.x * kQSlice, j1 = j0 + kQSlice < q.k_total ? j0 + kQSlice : q.k_total;
     const bool own = q.qkind == kQuantSignMean;
-    uint32_t t = 0;
     float x[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const uint64_t j = j0 + i * kBlock + tid;
         x[i] = j < j1 ? q.val[j] : 0.0f;
     }
-    if (own) {  // tensor of slot j0: the last t with qbase[t] <= j0
-        uint32_t hi = q.T;
-        while (hi - t > 1) {
-            const uint32_t mid = (t + hi) >> 1;
-            if (q.qbase[mid] <= j0) t = mid;
-            else hi = mid;
-        }
-    }
-    for (uint64_t j = j0; j < j1;) {  // block-uniform walk over the tensors of the slice
-        while (own && q.qbase[t + 1] <= j) ++t;
-        const uint64_t e = own && q.qbase[t + 1] < j1 ? q.qbase[t + 1] : j1;
+    const auto base = [&](uint32_t t) { return q.qbase[t]; };
+    const uint32_t t0 = own ? wave_last_at_most(base, q.T, (uint32_t)j0) : 0u;
+    if (!own || q.qbase[t0 + 1] >= j1) {  // (block-uniform)
         double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const uint64_t at = j0 + i * kBlock + tid;
-            if (at >= j && at < e) add_value(v, x[i]);
-        }
+        for (int i = 0; i < PER; ++i)
+            if (j0 + i * kBlock + tid < j1) add_value(v, x[i]);
         block_sum4<kBlock>(v, lds);
         if (tid == 0)
-            for (int i = 0; i < 4; ++i) q.tq[4 * ((size_t)blockIdx.x + t) + i] = v[i];
-        j = e;
+            for (int i = 0; i < 4; ++i) q.tq[4 * ((size_t)blockIdx.x + t0) + i] = v[i];
+        return;
+    }
+    const uint32_t t1 = wave_last_at_most(base, q.T, (uint32_t)(j1 - 1));
+    if (tid == 0) nmore = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) xs[i * kBlock + tid] = x[i];
+    __syncthreads();
+    for (uint32_t t = t0 + tid; t <= t1; t += kBlock) {
+        const uint32_t b = q.qbase[t] > j0 ? q.qbase[t] - (uint32_t)j0 : 0u;
+        const uint32_t e = (uint32_t)((q.qbase[t + 1] < j1 ? q.qbase[t + 1] : j1) - j0);
+        if (b >= e) continue;  // no entry of its own: nobody reads the record
+        if (e - b > kQThreadSum) {
+            more[atomicAdd(&nmore, 1u)] = t;
+            continue;
+        }
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (uint32_t i = b; i < e; ++i) add_value(v, xs[i]);
+        for (int i = 0; i < 4; ++i) q.tq[4 * ((size_t)blockIdx.x + t) + i] = v[i];
+    }
+    __syncthreads();
+    for (uint32_t d = wave_index(); d < nmore; d += kWavesPerBlock) {
+        const uint32_t t = more[d];
+        const uint32_t b = q.qbase[t] > j0 ? q.qbase[t] - (uint32_t)j0 : 0u;
+        const uint32_t e = (uint32_t)((q.qbase[t + 1] < j1 ? q.qbase[t + 1] : j1) - j0);
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (uint32_t i = b + lane_id(); i < e; i += kWave) add_value(v, xs[i]);
+        for (int i = 0; i < 4; ++i) {
+            v[i] = wave_sum(v[i]);
+            if (lane_id() == 0) q.tq[4 * ((size_t)blockIdx.x + t) + i] = v[i];
+        }
+    }
+}
+
+// The centres of tensor t under threshold centres: the smallest kept magnitude
+// of the segment is the exact threshold key.
+__device__ __forceinline__ void threshold_centres(const QuantArgs& q, uint32_t t, float& pos, float& neg) {
+    const uint32_t s = q.per_tensor ? t : 0u;
+    pos = neg = 0.0f;
+    if (keep_of(q.seg_off[s + 1] - q.seg_off[s], q.keep_ppm) > 0) {
+        pos = __uint_as_float(q.seg[s].thr);
+        neg = __uint_as_float(q.seg[s].thr | 0x80000000u);
+    }
+}
+__device__ __forceinline__ void mean_centres(const double v[4], float& pos, float& neg) {
+    pos = v[2] > 0.0 ? (float)(v[0] / v[2]) : 0.0f;
+    neg = v[3] > 0.0 ? (float)(v[1] / v[3]) : 0.0f;
+}
+
+// Centres per tensor of more than kMeansLocalT tensors (sign means from the
+// slices' sums, threshold centres), a wave each: few entries or records to a
+// tensor, so blocks of their own were mostly launch.
+__global__ __launch_bounds__(kBlock) void k_tmeans(QuantArgs q) {
+    const uint32_t t = blockIdx.x * kWavesPerBlock + wave_index();
+    if (t >= q.T) return;
+    float pos, neg;
+    if (q.qkind == kQuantThreshold) {
+        threshold_centres(q, t, pos, neg);
+    } else {
+        const uint32_t a = q.qbase[t], b = q.qbase[t + 1];
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (uint32_t r = a / kQSlice + lane_id(); a < b && r <= (b - 1) / kQSlice; r += kWave)
+            for (int i = 0; i < 4; ++i) v[i] += q.tq[4 * ((size_t)r + t) + i];
+        for (int i = 0; i < 4; ++i) v[i] = wave_sum(v[i]);
+        mean_centres(v, pos, neg);
+    }
+    if (lane_id() == 0) {
+        q.means[2 * t + 0] = pos;
+        q.means[2 * t + 1] = neg;
     }
 }
 
@@ -212,12 +292,7 @@ __global__ __launch_bounds__(kMeansThreads) void k_dmeans(QuantArgs q, uint32_t 
     if (q.qkind == kQuantColumnMean) return;
     float pos = 0.0f, neg = 0.0f;
     if (q.qkind == kQuantThreshold) {
-        // the smallest kept magnitude of the segment is the exact threshold key
-        const uint32_t s = q.per_tensor ? t : 0u;
-        if (keep_of(q.seg_off[s + 1] - q.seg_off[s], q.keep_ppm) > 0) {
-            pos = __uint_as_float(q.seg[s].thr);
-            neg = __uint_as_float(q.seg[s].thr | 0x80000000u);
-        }
+        threshold_centres(q, t, pos, neg);
     } else {
         const bool own = q.qkind == kQuantSignMean;
         const uint32_t a = own ? qbase[t] : 0u, b = own ? qbase[t + 1] : qbase[q.T];
@@ -236,8 +311,7 @@ __global__ __launch_bounds__(kMeansThreads) void k_dmeans(QuantArgs q, uint32_t 
             }
         }
         block_sum4<NT>(v, lds);
-        pos = v[2] > 0.0 ? (float)(v[0] / v[2]) : 0.0f;
-        neg = v[3] > 0.0 ? (float)(v[1] / v[3]) : 0.0f;
+        mean_centres(v, pos, neg);
     }
     if (tid == 0) {
         q.means[2 * t + 0] = pos;
@@ -387,11 +461,14 @@ hipError_t launch_quant(const QuantArgs& q, hipStream_t st) {
     const bool local = column && q.T <= kColLocalT;  // k_colsum finds the first slots itself
     if (!local && q.direct) {
         const bool sums = q.qkind == kQuantSignMean || q.qkind == kQuantGlobalMean;
-        const bool sliced = sums && q.k_total > kMeansDirectK, base = sliced || q.T > kMeansLocalT;
+        const bool many = q.T > kMeansLocalT, own = q.qkind != kQuantGlobalMean;
+        const bool sliced = sums && (q.k_total > kMeansDirectK || (many && own && q.k_total > 0)), base = sliced || many;
         if (base) hipLaunchKernelGGL(k_qbase, dim3(1), dim3(kMeansThreads), 0, st, q);
         if (sliced) hipLaunchKernelGGL(k_qsum, dim3((uint32_t)((q.k_total + kQSlice - 1) / kQSlice)), dim3(kBlock), 0, st, q);
         // (column means need the first slots only, of one block)
-        if (!column || !base)
+        if (!column && many && own)
+            hipLaunchKernelGGL(k_tmeans, dim3(blocks_for_waves(q.T)), dim3(kBlock), 0, st, q);
+        else if (!column || !base)
             hipLaunchKernelGGL(k_dmeans, dim3(column ? 1u : q.T), dim3(kMeansThreads), 0, st, q, sliced ? 1u : 0u,
                                base ? 1u : 0u);
     } else if (!local) {

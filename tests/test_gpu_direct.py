@@ -95,3 +95,20 @@ def test_pull_from_copy(n):
             assert np.array_equal(out.val[:out.k].cpu().numpy().view(np.uint32), o.val.view(np.uint32))
             assert np.array_equal(ct.cpu().numpy().view(np.uint32), oc.view(np.uint32))
             assert np.array_equal(out.tensor_counts[:comp.T].cpu().numpy().view(np.uint32), o.tensor_counts)
+
+
+@pytest.mark.parametrize("quant", [gd.GD_QUANT_SIGN_MEAN, gd.GD_QUANT_GLOBAL_MEAN, gd.GD_QUANT_THRESHOLD],
+                         ids=["sign_mean", "global_mean", "threshold"])
+@pytest.mark.parametrize("tensors", [3, 900, 1023, 1024, 5000])
+def test_sums_over_many_tensors(tensors, quant):
+    # slices of 4,096 sent entries inside one tensor, across a few and across
+    # thousands (empty ones among them): tensors of at most and more than 32
+    # entries in a slice, one that spans several slices, few entries in all
+    rng = np.random.default_rng(tensors)
+    sizes = rng.choice([0, 1, 5, 31, 32, 33, 64, 400], tensors)
+    sizes[rng.integers(0, tensors, 2)] = [30_000, 6_000]
+    off = [0] + np.cumsum(sizes).tolist()
+    g = rng.normal(0, 1e-3, off[-1]).astype(np.float32)
+    comp = gd.Compressor(off)
+    for per, drop in ((False, 0.0), (True, 0.0), (False, 0.3), (True, 0.5), (False, 0.99), (False, 1.0)):
+        check_case(g, np.zeros_like(g), off, drop, per, quant, comp=comp, what=f"T={tensors} per={per} drop={drop}")
