@@ -46,3 +46,17 @@ def test_columns(columns, rows, drop):
 def test_many_entries(n, drop):
     # up to and past 2^20 entries, in the direct and the candidate form
     _run([n - 1024, 1024], [64, 1024], (drop,), 1, pers=(False,))
+
+
+@pytest.mark.parametrize("tensors", [200, 3000])
+@pytest.mark.parametrize("drop", [0.0, 0.5])
+def test_many_tensors_in_a_slice(tensors, drop):
+    # slices that span many tensors: of as many entries as columns and one less, of
+    # twice as many (what slices of 4,096 sum on chip), none, and one large
+    # tensor among them; up to and past 2^16, 2^18 and 2^20 entries in all
+    rng = np.random.default_rng(tensors)
+    for scale in (1, 4, 20) if tensors == 200 else (1, 3):
+        cols = rng.choice([1, 2, 3, 8, 100], tensors)
+        sizes = cols * rng.choice([0, 1, 2, 3, 40], tensors) * scale
+        sizes[5], cols[5] = 100_000 * scale, 400
+        _run(sizes, cols.tolist(), (drop,), tensors + scale, pers=(False,))
