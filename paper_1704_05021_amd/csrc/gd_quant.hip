@@ -353,12 +353,15 @@ __global__ __launch_bounds__(kBlock) void k_colsum(QuantArgs q) {
     const uint64_t j0 = (uint64_t)blockIdx.x * kSlice;
     float x[PER];
     uint32_t ix[PER];
+    const auto load = [&] {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const uint64_t at = j0 + i * kBlock + tid;
-        x[i] = at < q.k_total ? __uint_as_float(load_early(reinterpret_cast<const uint32_t*>(q.val) + at)) : 0.0f;
-        ix[i] = at < q.k_total ? load_early(q.idx + at) : 0u;
-    }
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t at = j0 + i * kBlock + tid;
+            x[i] = at < q.k_total ? __uint_as_float(load_early(reinterpret_cast<const uint32_t*>(q.val) + at)) : 0.0f;
+            ix[i] = at < q.k_total ? load_early(q.idx + at) : 0u;
+        }
+    };
+    if (!q.sampled) load();
     if (LOCAL) {
         uint32_t all;
         const uint32_t excl = block_excl_scan<kBlock>((uint32_t)tid < q.T ? q.tensor_counts[tid] : 0u, scan, &all);
@@ -369,6 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_colsum(QuantArgs q) {
     const auto base = [&](uint32_t t) { return LOCAL ? first[t] : q.qbase[t]; };
     const uint32_t total = base(q.T);
     if (j0 >= total) return;
+    if (q.sampled) load();  // (most blocks of a large capacity lie past what is sent)
     const uint32_t j1 = j0 + kSlice < total ? (uint32_t)j0 + kSlice : total;
     const auto clear = [&](uint32_t n) {
         for (uint32_t i = tid; i < n; i += kBlock) {
@@ -487,7 +491,11 @@ static inline uint32_t blocks_for_waves(uint32_t waves) { return (waves + kWaves
 
 hipError_t launch_quant(const QuantArgs& q, hipStream_t st) {
     const bool column = q.qkind == kQuantColumnMean;
-    const bool local = column && q.T <= kColLocalT;  // k_colsum finds the first slots itself
+    // k_colsum finds the first slots itself, but where most of its blocks may only
+    // find that they lie past the entries sent (40M elements, a capacity of all of
+    // them, 400,000 sent: 245 us a call, with the first slots by a pass of their
+    // own and no values read there 170)
+    const bool local = column && q.T <= kColLocalT && !(q.sampled && q.k_total > kColMidK);
     if (!local && q.direct) {
         const bool sums = q.qkind == kQuantSignMean || q.qkind == kQuantGlobalMean;
         const bool many = q.T > kMeansLocalT, own = q.qkind != kQuantGlobalMean;
@@ -508,8 +516,10 @@ hipError_t launch_quant(const QuantArgs& q, hipStream_t st) {
         // adds to columns that many blocks share (a call with slices of 1,024 /
         // 2,048 / 4,096 in us: 120,000 entries over 200 columns x 6 tensors 94 /
         // 96 / 100; 21,000 ragged ones 100 / 103 / 111, of 256 98; 960,000 over 8
-        // 132 / 126 / 124; 4.25M over 500 381 / 336 / 322).
-        const uint32_t per = q.k_total <= kColTinyK ? 1u : q.k_total <= kColSmallK ? 4u : q.k_total <= kColMidK ? 8u : 16u;
+        // 132 / 126 / 124; 4.25M over 500 381 / 336 / 322).  Under a sampled
+        // threshold k_total is only a bound, and often far above what is sent (this
+        // pass at 50,000 sent of 5M in slices of 2,048 / 4,096: 11.5 / 14.5 us).
+        const uint32_t per = q.k_total <= kColTinyK ? 1u : q.k_total <= kColSmallK ? 4u : q.k_total <= kColMidK || q.sampled ? 8u : 16u;
         const uint32_t slice = per * kBlock;
         const dim3 g((uint32_t)((q.k_total + slice - 1) / slice));
         auto sums = per == 1   ? (local ? k_colsum<1, true> : k_colsum<1, false>)

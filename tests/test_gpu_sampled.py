@@ -298,3 +298,17 @@ def test_random_cases(block):
               what=f"case {case}: N={N} T={T} {kind} drop={drop} per={per} ppm={ppm} q={q} cap={cap} "
                    f"base={base is not None}")
         comp.close()
+
+
+@pytest.mark.parametrize("capacity", [1 << 20, (1 << 20) + 1, 1_300_000])
+def test_column_centres_under_a_large_capacity(capacity):
+    # a capacity far above what is sent: the first slots are found by the column sums
+    # up to 2^20 slots and by a pass of their own past them, and most slices hold nothing
+    rng = np.random.default_rng(90)
+    offsets, cols = [0, 500_000, 500_000, 1_300_000], [500, 3, 80]
+    g, r = _values(rng, offsets[-1], "heavy"), _values(rng, offsets[-1], "gauss")
+    comp = gd.Compressor(offsets)
+    comp.set_columns(cols)
+    for per, drop in ((False, 0.99), (True, 0.9), (False, 0.0)):
+        check(g, r, offsets, drop, per, 10_000, 3, capacity=capacity, comp=comp, quant=gd.GD_QUANT_COLUMN_MEAN,
+              columns=cols, what=f"capacity={capacity} per={per} drop={drop}")
