@@ -425,11 +425,18 @@ gd_status gd_create(gd_ctx** out, const uint64_t* off, uint32_t T) {
          dev_alloc(ctx, &ctx->scr.skeys, std::max(ctx->skeys_tensor, ctx->skeys_global)) &&
          dev_alloc(ctx, &ctx->scr.qbase, T + 1) && dev_alloc(ctx, &ctx->scr.shist, (size_t)S_max * gd::kSHistWords) &&
          dev_alloc(ctx, &ctx->scr.sshist, (size_t)S_max * gd::kSsCopies * gd::kSsNB0);
-    const bool direct = C <= gd::kDirectMaxUnits;  // larger layouts never take the direct form
-    const size_t h_words = direct ? (size_t)S_max * gd::hist_copies(T) * gd::kSelBins : 0;
-    ok = ok && dev_alloc(ctx, &ctx->scr.tq, direct ? 4 * (size_t)(N / gd::kQSlice + 1 + T) : 0) &&
-         dev_alloc(ctx, &ctx->scr.info, gd::direct_pieces(C, T)) && dev_alloc(ctx, &ctx->scr.h0, h_words) &&
-         dev_alloc(ctx, &ctx->scr.h1, h_words);
+    if (C <= gd::kDirectMaxUnits) {  // larger layouts never take the direct form
+        ok = ok && dev_alloc(ctx, &ctx->scr.tq, 4 * (size_t)(N / gd::kQSlice + 1 + T)) &&
+             dev_alloc(ctx, &ctx->scr.info, gd::direct_pieces(C, T));
+        // Its histograms are those of the other forms, one call at a time using
+        // either: the first digit's the sampled mode's, which both leave clear, the
+        // second digit's the candidate form's, which both clear at the start.
+        static_assert(gd::kHistCopies * gd::kSelBins == gd::kSsCopies * gd::kSsNB0 &&
+                          gd::kHistCopies * gd::kSelBins <= gd::kHistWords,
+                      "one segment's histogram copies fit");
+        ctx->scr.h0 = ctx->scr.sshist;
+        ctx->scr.h1 = ctx->scr.hist;
+    }
     if (!ok) {
         free_all(ctx);
         delete ctx;
@@ -441,7 +448,6 @@ gd_status gd_create(gd_ctx** out, const uint64_t* off, uint32_t T) {
         return GD_ERR_OOM;
     }
     if (hipMemset(ctx->scr.seg, 0, S_max * sizeof(gd::SegState)) != hipSuccess ||
-        (h_words && hipMemset(ctx->scr.h0, 0, h_words * sizeof(uint32_t)) != hipSuccess) ||
         hipMemset(ctx->scr.shist, 0, (size_t)S_max * gd::kSHistWords * sizeof(uint32_t)) != hipSuccess ||
         hipMemset(ctx->scr.sshist, 0, (size_t)S_max * gd::kSsCopies * gd::kSsNB0 * sizeof(uint32_t)) != hipSuccess ||
         hipMemset(ctx->scr.ten_cbase, 0, (T + 1) * sizeof(uint32_t)) != hipSuccess ||

@@ -57,10 +57,10 @@ struct Scratch {
     uint32_t* shist = nullptr;       // [S_max * kSHistWords] sample histograms, kept zero between calls
     uint32_t* qbase = nullptr;       // [T + 1] first output slot of each tensor
     PieceInfo* info = nullptr;       // direct form: [pieces]
-    uint32_t* h0 = nullptr;          // [S_max * copies * kSelBins] its first digit; clear between calls
-    uint32_t* h1 = nullptr;          // [S_max * copies * kSelBins] its second digit
+    uint32_t* h0 = nullptr;          // [S_max * copies * kSelBins] its first digit; clear between calls (gd_create: sshist)
+    uint32_t* h1 = nullptr;          // [S_max * copies * kSelBins] its second digit (gd_create: hist)
     double* tq = nullptr;            // [(N / kQSlice + 1 + T) * 4] its quantisation sums
-    uint32_t* sshist = nullptr;      // [S_max * kSsCopies * kSsNB0] sampled mode: top-digit histograms
+    uint32_t* sshist = nullptr;      // [S_max * kSsCopies * kSsNB0] sampled mode: top-digit histograms, clear between calls
 };
 
 // Column-wise centres: each tensor's matrix view and the per-column sums.

@@ -1,5 +1,5 @@
 """The library's host code without a GPU: a stub of the HIP runtime calls that
-an apply makes, loaded ahead of the runtime in a child process, which records
+gd_create and an apply make, loaded ahead of the runtime in a child process, which records
 allocations and launches in place of making them.  Tests pass child code that
 uses the names below; kernels never run, so pointers may hold anything."""
 import os
@@ -15,10 +15,14 @@ STUB = r"""
 typedef struct { uint32_t x, y, z; } dim3_t;
 int g_launches, g_allocs, g_frees, g_captured_stream, g_other_capture, g_refused, g_mode;
 uintptr_t g_last_alloc, g_last_free, g_next = 0x10000000;
-size_t g_last_size;
+size_t g_last_size, g_total;
 dim3_t g_grid;
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipGetLastError(void) { return 0; }
+int hipSetDevice(int d) { return d; }
+int hipDeviceSynchronize(void) { return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int kind) { return 0; }
+int hipMemset(void* d, int v, size_t n) { return 0; }
 int hipStreamIsCapturing(void* s, int* status) {
     *status = g_captured_stream && (uintptr_t)s == (uintptr_t)g_captured_stream;
     return 0;
@@ -33,7 +37,8 @@ int hipThreadExchangeStreamCaptureMode(int* mode) {
 // in the global mode (0) and breaks; a thread in the relaxed mode (2) may allocate.
 int hipMalloc(void** p, size_t n) {
     if ((g_captured_stream || g_other_capture) && g_mode != 2) { ++g_refused; return 900; }
-    g_last_alloc = g_next; g_last_size = n; g_next += (n + 4095) & ~(size_t)4095; ++g_allocs;
+    g_last_alloc = g_next; g_last_size = n; g_total += n;
+    g_next += (n + 4095) & ~(size_t)4095; ++g_allocs;
     *p = (void*)g_last_alloc;
     return 0;
 }
@@ -58,6 +63,15 @@ S = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
 L = ctypes.CDLL({lib!r})
 vp, u64, u32, i32 = ctypes.c_void_p, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int
 L.gd_apply_sparse.argtypes = [vp, u64, u32, vp, vp, vp, ctypes.c_float, vp]
+L.gd_create.argtypes = [ctypes.POINTER(vp), vp, u32]
+L.gd_destroy.argtypes = [vp]
+def create(offsets):
+    "Device bytes that gd_create allocates for a layout, and the allocations it makes."
+    h, before, count = vp(), get("g_total", u64), get("g_allocs")
+    st = L.gd_create(ctypes.byref(h), (u64 * len(offsets))(*offsets), len(offsets) - 1)
+    assert st == 0, st
+    L.gd_destroy(h)
+    return get("g_total", u64) - before, get("g_allocs") - count
 def get(name, t=i32): return t.in_dll(S, name).value
 def put(name, v): i32.in_dll(S, name).value = v
 def apply(n, clients, nnz, stream=16):
