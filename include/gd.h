@@ -350,7 +350,9 @@ gd_status gd_debug_apply_form(int form);
  * bracket lo and hi, candidate count, bracket-miss flag, radix digits and
  * ranks, threshold key, ties kept, zero-mode flag: fewer nonzero keys than
  * k, so the threshold is key 0) for up to max_segments segments into
- * seg_words (host), and the decomposition into info (host, 4 entries:
+ * seg_words (host; a segment that keeps nothing has the threshold key 2^32 - 1;
+ * a layout small enough for the direct form has no candidates: the count is that
+ * of the nonzero keys and the bracket is an earlier call's), and the decomposition into info (host, 4 entries:
  * elements per dense-pass unit, units, candidates per tile, most tiles).
  * Synchronises the host.
  */

@@ -190,11 +190,12 @@ __device__ __forceinline__ void hist_add_wave(uint32_t* h, uint32_t bin, bool ac
 }
 
 // The per-call state that does not depend on the data: the first output slot
-// of each segment, and where one segment is one tensor the kept counts.
+// of each segment, where one segment is one tensor the kept counts, and the
+// state of the segments that keep nothing, which no later pass touches.
 // Run by one block.
 template <int NT>
 __device__ __forceinline__ void call_prologue(const uint32_t* seg_off, uint32_t S, uint32_t T, uint32_t keep_ppm,
-                                              uint64_t* out_base, uint32_t* tensor_counts,
+                                              uint64_t* out_base, uint32_t* tensor_counts, SegState* seg,
                                               uint32_t* lds) {
     const int tid = threadIdx.x;
     const bool own = S == T;  // a segment is a tensor: k is its kept count
@@ -207,6 +208,11 @@ __device__ __forceinline__ void call_prologue(const uint32_t* seg_off, uint32_t 
         if (s < S) {
             out_base[s] = carry + excl;
             if (own) tensor_counts[s] = k;
+            if (k == 0) {
+                SegState& g = seg[s];
+                g.clo = g.miss = g.need = g.zero = 0;
+                g.thr = kNoKey;
+            }
         }
         carry += total;
     }
@@ -706,7 +712,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_dacc(DirectArgs a) {
         uint4* z = reinterpret_cast<uint4*>(a.h1);
         for (size_t i = (size_t)blockIdx.x * NT + tid; i < words; i += (size_t)gridDim.x * NT) z[i] = make_uint4(0u, 0u, 0u, 0u);
     }
-    if (blockIdx.x == 0) call_prologue<NT>(a.seg_off, a.S, a.T, a.keep_ppm, a.out_base, a.tensor_counts, lds);
+    if (blockIdx.x == 0) call_prologue<NT>(a.seg_off, a.S, a.T, a.keep_ppm, a.out_base, a.tensor_counts, a.seg, lds);
     Piece p;
     if (!piece_of(a, blockIdx.x, p)) return;
     const uint32_t c = p.c;

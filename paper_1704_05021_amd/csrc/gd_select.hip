@@ -435,6 +435,10 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(SampleArgs a) {
     if (tid == 0) {
         a.seg[s].lo = lo;
         a.seg[s].hi = hi;
+        if (k == 0) {  // (no later pass finds a candidate here)
+            a.seg[s].thr = kNoKey;
+            a.seg[s].need = 0;
+        }
     }
 }
 

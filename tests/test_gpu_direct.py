@@ -112,3 +112,20 @@ def test_sums_over_many_tensors(tensors, quant):
     comp = gd.Compressor(off)
     for per, drop in ((False, 0.0), (True, 0.0), (False, 0.3), (True, 0.5), (False, 0.99), (False, 1.0)):
         check_case(g, np.zeros_like(g), off, drop, per, quant, comp=comp, what=f"T={tensors} per={per} drop={drop}")
+
+
+@pytest.mark.parametrize("debug", [0, 1], ids=["direct", "candidates"])
+def test_state_of_segments_that_keep_nothing(debug):
+    # 50 entries at 99% drop, and an empty tensor: the state is this call's, not an
+    # earlier one's that kept half of them
+    off = [0, 50, 50, 100_000]
+    rng = np.random.default_rng(5)
+    g = np.zeros(off[-1], np.float32)
+    g[::7] = rng.normal(0, 1, g[::7].size).astype(np.float32)  # half kept needs zeros
+    comp = gd.Compressor(off)
+    for drop in (0.5, 0.99):
+        check_case(g, np.zeros_like(g), off, drop, True, False, comp=comp, debug_bracket=debug, what=f"drop={drop}")
+    segs = comp.debug_state()[0]
+    for s in segs[:2]:
+        assert (s["thr"], s["need"], s["zero"], s["miss"], s["clo"]) == (0xFFFFFFFF, 0, 0, 0, 0), s
+    assert segs[2]["thr"] not in (0, 0xFFFFFFFF) and segs[2]["zero"] == 0
