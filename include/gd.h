@@ -326,7 +326,8 @@ gd_status gd_profile_read(gd_ctx* ctx, double* dense_ms, uint64_t* dense_launche
  * candidate; 3: every element is a candidate; 4: only keys at or above the
  * point estimate are candidates and all of them are zeroed, so about half
  * the segments take the exact fallback after the dense pass has zeroed
- * part of their residual.  GD_ERR_ARG for other modes.
+ * part of their residual; 5: the sample's own bracket (small layouts are kept
+ * on the sampled path, as under every mode but 0).  GD_ERR_ARG for other modes.
  */
 gd_status gd_debug_force_bracket(gd_ctx* ctx, int mode);
 
@@ -352,7 +353,8 @@ gd_status gd_debug_apply_form(int form);
  * k, so the threshold is key 0) for up to max_segments segments into
  * seg_words (host; a segment that keeps nothing has the threshold key 2^32 - 1;
  * a layout small enough for the direct form has no candidates: the count is that
- * of the nonzero keys and the bracket is an earlier call's), and the decomposition into info (host, 4 entries:
+ * of the nonzero keys and the bracket is an earlier call's; the last word is the
+ * form of the call: 1 direct, 2 candidates under an exact threshold, 3 sampled), and the decomposition into info (host, 4 entries:
  * elements per dense-pass unit, units, candidates per tile, most tiles).
  * Synchronises the host.
  */

@@ -265,7 +265,8 @@ gd_status compress_exact(gd_ctx* ctx, const float* grad, const float* base, floa
     const uint32_t ppm = (uint32_t)keep_ppm_of(drop_ratio);
     const uint32_t* seg_off = per ? ctx->tab.tensor_off : ctx->tab.global_off;
     const uint32_t S = per ? ctx->T : 1u;
-    if (ctx->num_units <= kDirectMaxUnits && ctx->debug_bracket == 0) {
+    ctx->last_form = ctx->num_units <= kDirectMaxUnits && ctx->debug_bracket == 0 ? kFormDirect : kFormCandidates;
+    if (ctx->last_form == kFormDirect) {
         DirectArgs a{};
         a.grad = grad;
         a.base = base;
@@ -547,6 +548,7 @@ gd_status gd_compress_sampled(gd_ctx* ctx, const float* grad, const float* base,
     }
     const uint64_t max_samples = (max_n * sample_ppm + 999999u) / 1000000u;
 
+    ctx->last_form = gd::kFormSampled;
     gd::SampledArgs sa{};
     sa.grad = grad;
     sa.base = base;
@@ -634,7 +636,7 @@ gd_status gd_debug_apply_form(int form) {
 }
 
 gd_status gd_debug_force_bracket(gd_ctx* ctx, int mode) {
-    if (!ctx || mode < 0 || mode > 4) return GD_ERR_ARG;
+    if (!ctx || mode < 0 || mode > 5) return GD_ERR_ARG;
     ctx->debug_bracket = (uint32_t)mode;
     return GD_OK;
 }
@@ -651,6 +653,8 @@ gd_status gd_debug_state(gd_ctx* ctx, uint32_t* seg_words, uint32_t max_segments
     if (hipDeviceSynchronize() != hipSuccess) return GD_ERR_HIP;
     if (hipMemcpy(seg_words, ctx->scr.seg, n * sizeof(gd::SegState), hipMemcpyDeviceToHost) != hipSuccess)
         return GD_ERR_HIP;
+    constexpr uint32_t words = sizeof(gd::SegState) / sizeof(uint32_t);
+    for (uint32_t s = 0; s < n; ++s) seg_words[words * s + words - 1] = ctx->last_form;
     return GD_OK;
 }
 

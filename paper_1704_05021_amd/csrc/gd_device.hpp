@@ -104,7 +104,7 @@ struct SegState {
     uint32_t runs;  // kept between calls: 1 when the last sample's units counted like independent
                     // draws, so the next call samples one run of 16 neighbours per unit
     uint32_t blo;   // direct form: first of the 512 keys that hold the threshold key (zero mode: 0)
-    uint32_t pad[3];
+    uint32_t pad[3];  // (gd_debug_state reports the call's form in the last word)
 };
 
 __device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }

@@ -89,6 +89,9 @@ uint32_t direct_pieces(uint32_t C, uint32_t T);
 // Copies of each segment's histograms in a layout of T tensors.
 inline uint32_t hist_copies(uint32_t T) { return T <= kCopiesMaxT ? (uint32_t)kHistCopies : 1u; }
 
+// The forms of a compression, as gd_debug_state reports them.
+constexpr uint32_t kFormDirect = 1, kFormCandidates = 2, kFormSampled = 3;
+
 // The launch sequence of one exact-threshold compression (the direct form, or
 // sample, bracket, dense pass and candidate passes; then quantisation) on the
 // tables and scratch ctx points to, after the caller's argument checks;
@@ -111,7 +114,8 @@ struct gd_ctx {
     gd::Scratch scr;
     gd::ColumnTables cols;
     std::vector<void*> allocations;
-    uint32_t debug_bracket = 0;
+    uint32_t debug_bracket = 0;  // gd_debug_force_bracket's mode
+    uint32_t last_form = 0;      // form of the last call (gd_debug_state)
     uint32_t profile_every = 0;  // time dense launches 0, every, 2 * every, ... (0: off)
     std::vector<hipEvent_t> events;  // pairs
     size_t events_used = 0;

@@ -8,7 +8,8 @@
 
 namespace gd {
 
-// Host-forced brackets, to exercise the paths a real sample rarely takes.
+// Host-forced brackets, to exercise the paths a real sample rarely takes
+// (gd_debug_force_bracket's mode 5 leaves the sample's own).
 constexpr uint32_t kDebugLoTooHigh = 1;  // no candidates: every segment takes the fallback
 constexpr uint32_t kDebugHiAtLo = 2;     // zero every candidate in the dense pass
 constexpr uint32_t kDebugLoZero = 3;     // every element is a candidate

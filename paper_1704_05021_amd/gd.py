@@ -337,7 +337,7 @@ class Compressor:
         st = _lib().gd_debug_state(self._h, words.ctypes.data, self.T, info.ctypes.data)
         if st != 0:
             raise GDError(st, "gd_debug_state")
-        segs = [dict(zip(self.SEG_FIELDS, (int(x) for x in row[:len(self.SEG_FIELDS)]))) for row in words]
+        segs = [dict(zip(self.SEG_FIELDS, (int(x) for x in row[:len(self.SEG_FIELDS)])), form=int(row[-1])) for row in words]
         keys = ("unit_len", "units", "tile", "max_tiles")
         return segs, dict(zip(keys, (int(x) for x in info)))
 

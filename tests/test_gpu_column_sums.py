@@ -21,8 +21,9 @@ def _run(sizes, cols, drops, seed, pers=(False, True)):
     comp.set_columns(cols)
     for drop in drops:
         for per in pers:
-            check_case(g, r, off, drop, per, gd.GD_QUANT_COLUMN_MEAN, comp=comp, columns=cols,
-                       what=f"T={len(sizes)} drop={drop} per={per}")
+            for debug in (0, 5):  # the direct form's list, and the candidate form's
+                check_case(g, r, off, drop, per, gd.GD_QUANT_COLUMN_MEAN, comp=comp, columns=cols, debug_bracket=debug,
+                           what=f"T={len(sizes)} drop={drop} per={per} debug={debug}")
 
 
 @pytest.mark.parametrize("tensors", [1, 2, 254, 255, 256, 1100])

@@ -56,7 +56,8 @@ def _tie_heavy(rng, n):
     return v.astype(np.float32)
 
 
-@pytest.mark.parametrize("debug", [0, 1, 2, 3, 4], ids=["sampled", "fallback", "zero_all_cands", "all_cands", "lo_at_hi"])
+@pytest.mark.parametrize("debug", [0, 5, 1, 2, 3, 4],
+                         ids=["direct", "sampled", "fallback", "zero_all_cands", "all_cands", "lo_at_hi"])
 @pytest.mark.parametrize("seed", range(6))
 def test_random_layouts(seed, debug):
     rng = np.random.default_rng(100 + seed)
@@ -88,7 +89,7 @@ def test_edge_sizes(n):
     r = rng.normal(0, 1, n).astype(np.float32)
     comp = gd.Compressor([0, n])
     for drop in (0.0, 0.5, 0.99, 1.0):
-        for debug in (0, 1):
+        for debug in (0, 5, 1):
             check_case(g, r, [0, n], drop, False, False, comp=comp, debug_bracket=debug,
                        what=f"n={n} drop={drop} debug={debug}")
 
@@ -109,8 +110,10 @@ def test_sparse_candidates_wide_windows():
         g[u * 1024 + (u * 37) % 1024] = (1.0 + u * 1e-4).astype(np.float32)  # one spike per unit
         for keep in (2900, 1024, 1025, 2048, 4000):
             drop = 1.0 - keep / n
-            for per in (False, True):
-                check_case(g, r, [0, n], drop, per, False, comp=comp, what=f"spikes noise={noise} keep={keep} per={per}")
+            for per, debug in ((False, 5), (True, 5), (True, 0)):
+                check_case(g, r, [0, n], drop, per, False, comp=comp, debug_bracket=debug,
+                           what=f"spikes noise={noise} keep={keep} per={per} debug={debug}")
+                assert comp.debug_state()[0][0]["form"] == (2 if debug else 1)
                 if noise == 0.0 and keep > units:
                     # fewer nonzero keys than k: every spike, and nothing else, is a
                     # candidate (one per unit, so a full tile's window holds 1024
@@ -122,7 +125,9 @@ def test_sparse_candidates_wide_windows():
     offsets = [0, n // 3, n]
     comp2 = gd.Compressor(offsets)
     for drop, per, quant in ((0.9995, False, False), (0.9995, True, False), (0.999, False, True)):
-        check_case(g2, r2, offsets, drop, per, quant, comp=comp2, what=f"sparse drop={drop} per={per} q={quant}")
+        for debug in (0, 5):
+            check_case(g2, r2, offsets, drop, per, quant, comp=comp2, debug_bracket=debug,
+                       what=f"sparse drop={drop} per={per} q={quant} debug={debug}")
 
 
 def test_unaligned_tensor_offsets():
@@ -135,7 +140,7 @@ def test_unaligned_tensor_offsets():
     comp = gd.Compressor(offsets)
     for per in (False, True):
         for quant in (False, True):
-            for debug in (0, 1, 2, 3, 4):
+            for debug in (0, 1, 2, 3, 4, 5):
                 check_case(g, r, offsets, 0.9, per, quant, comp=comp, debug_bracket=debug, what=f"per={per} q={quant}")
 
 
@@ -144,7 +149,7 @@ def test_special_values():
     z = np.array([0.0, 0.0, 0.0, 0.0, 0.0, -0.0, -0.0, 2.0 ** -149, 0.0, -3.0], np.float32)
     comp = gd.Compressor([0, v.size])
     for drop in (0.0, 0.3, 0.5, 0.8, 0.9, 1.0):
-        for debug in (0, 1, 3):
+        for debug in (0, 5, 1, 3):
             check_case(v, z, [0, v.size], drop, False, False, comp=comp, debug_bracket=debug, what=f"drop={drop}")
 
 
@@ -153,9 +158,10 @@ def test_all_zero_and_all_equal():
     comp = gd.Compressor([0, 20000, n])
     z = np.zeros(n, np.float32)
     for per in (False, True):
-        check_case(z, z, [0, 20000, n], 0.99, per, False, comp=comp, what="zeros")
-        s = np.where(np.random.default_rng(1).random(n) < 0.5, -0.75, 0.75).astype(np.float32)
-        check_case(s, z, [0, 20000, n], 0.99, per, True, comp=comp, what="equal magnitudes")
+        for debug in (0, 5):
+            check_case(z, z, [0, 20000, n], 0.99, per, False, comp=comp, debug_bracket=debug, what="zeros")
+            s = np.where(np.random.default_rng(1).random(n) < 0.5, -0.75, 0.75).astype(np.float32)
+            check_case(s, z, [0, 20000, n], 0.99, per, True, comp=comp, debug_bracket=debug, what="equal magnitudes")
 
 
 def _run_workload(name, steps=None, debug=0):
@@ -182,6 +188,7 @@ def test_small_workloads(name):
     _run_workload(name)
     _run_workload(name, steps=2, debug=1)
     _run_workload(name, steps=2, debug=4)
+    _run_workload(name, steps=2, debug=5)
 
 
 @pytest.mark.slow
@@ -219,7 +226,7 @@ def test_pull_delta_base():
     p1[ix] -= rng.normal(0, 1e-2, 5000).astype(np.float32)
     res = np.zeros(n, np.float32)
     comp = gd.Compressor([0, n])
-    for debug in (0, 1):
+    for debug in (0, 5, 1):
         check_case(p1, res, [0, n], 0.99, False, False, base=p0, comp=comp, debug_bracket=debug, what="pull")
 
 
@@ -380,7 +387,9 @@ def test_many_tensors(T):
     r = rng.normal(0, 1e-3, N).astype(np.float32)
     comp = gd.Compressor(offsets)
     for per, quant, drop in ((True, False, 0.9), (False, False, 0.99), (True, True, 0.5)):
-        check_case(g, r, offsets, drop, per, quant, comp=comp, what=f"T={T} per={per} quant={quant}")
+        for debug in (0, 5):
+            check_case(g, r, offsets, drop, per, quant, comp=comp, debug_bracket=debug,
+                       what=f"T={T} per={per} quant={quant} debug={debug}")
 
 
 def test_empty_layout():

@@ -45,7 +45,7 @@ def check_pull(comp, params, copy, offsets, drop, per, debug=0, what=""):
     return c_want
 
 
-@pytest.mark.parametrize("debug", [0, 1, 3, 4], ids=["sampled", "fallback", "all_cands", "lo_at_hi"])
+@pytest.mark.parametrize("debug", [0, 5, 1, 3, 4], ids=["direct", "sampled", "fallback", "all_cands", "lo_at_hi"])
 @pytest.mark.parametrize("seed", range(3))
 def test_random_layouts(seed, debug):
     rng = np.random.default_rng(500 + seed)
@@ -117,7 +117,7 @@ def test_random_cases():
         params[same] = copy[same]
         drop = float(rng.choice([0.0, 0.5, 0.9, 0.99, 0.999, 1.0]))
         per = bool(rng.random() < 0.5)
-        debug = int(rng.choice([0, 0, 1, 3, 4]))
+        debug = int(rng.choice([0, 5, 1, 3, 4]))
         comp = gd.Compressor(offsets)
         check_pull(comp, params, copy, offsets, drop, per, debug,
                    what=f"case {case}: N={N} T={T} drop={drop} per={per} debug={debug}")

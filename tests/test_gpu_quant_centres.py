@@ -38,9 +38,10 @@ def divisor_columns(rng, sizes):
     return cols
 
 
+@pytest.mark.parametrize("debug", [0, 5], ids=["direct", "candidates"])
 @pytest.mark.parametrize("kind", list(KINDS))
 @pytest.mark.parametrize("seed", range(4))
-def test_random_layouts(kind, seed):
+def test_random_layouts(kind, seed, debug):
     rng = np.random.default_rng(300 + seed)
     T = int(rng.integers(1, 7))
     sizes = rng.integers(0, 60_000, T)
@@ -57,7 +58,7 @@ def test_random_layouts(kind, seed):
     comp.set_columns(cols)
     for per in (False, True):
         for drop in (0.99, 0.9):
-            check_case(g, r, offsets, drop, per, KINDS[kind], comp=comp, columns=cols,
+            check_case(g, r, offsets, drop, per, KINDS[kind], comp=comp, columns=cols, debug_bracket=debug,
                        what=f"{kind} seed={seed} per={per} drop={drop}")
 
 

@@ -50,6 +50,8 @@ def _case(case):
     per = bool(rng.random() < 0.5)
     quant = int(rng.choice([0, 0, 1, 2, 3, 4])) if rng.random() < 0.5 else 0
     debug = int(rng.choice([0, 0, 0, 1, 2, 3, 4]))
+    if debug == 0 and case % 2:
+        debug = 5  # the sample's own bracket, also where the layout is small enough for the direct form
     columns = None
     if quant == gd.GD_QUANT_COLUMN_MEAN:  # a divisor of each size
         columns = []

@@ -48,7 +48,7 @@ def _few_values(n: int, seed: int) -> np.ndarray:
     return (rng.integers(-8, 9, n) * 0.25).astype(np.float32)
 
 
-@pytest.mark.parametrize("debug", [0, 1, 3], ids=["sampled", "fallback", "all_cands"])
+@pytest.mark.parametrize("debug", [5, 1, 3], ids=["sampled", "fallback", "all_cands"])
 @pytest.mark.parametrize("drop", [0.99, 0.7])
 @pytest.mark.parametrize("per_tensor", [True, False], ids=["per_tensor", "global"])
 def test_grouped_segments_with_ties(per_tensor, drop, debug):
@@ -63,15 +63,17 @@ def test_grouped_segments_with_ties(per_tensor, drop, debug):
                what=f"few values per_tensor={per_tensor} drop={drop} debug={debug}")
 
 
+@pytest.mark.parametrize("debug", [0, 5], ids=["direct", "candidates"])
 @pytest.mark.parametrize("per_tensor", [True, False], ids=["per_tensor", "global"])
-def test_fp16_valued_ties_spread_over_bins(per_tensor):
+def test_fp16_valued_ties_spread_over_bins(per_tensor, debug):
     # fp16 keeps 10 mantissa bits: candidates that share the threshold's first
     # 18 key bits fall in two digit-2 bins, so both the run and the
     # one-by-one counting take part
     rng = np.random.default_rng(12)
     off = [0, 3_000_000, 3_500_000, 6_000_000]
     g = rng.standard_normal(off[-1]).astype(np.float16).astype(np.float32)
-    check_case(g, np.zeros_like(g), off, 0.99, per_tensor, False, what=f"fp16-valued per_tensor={per_tensor}")
+    check_case(g, np.zeros_like(g), off, 0.99, per_tensor, False, debug_bracket=debug,
+               what=f"fp16-valued per_tensor={per_tensor}")
 
 
 def test_grouped_segment_with_quantised_centres():
