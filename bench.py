@@ -431,6 +431,15 @@ def main_shard(args, torch, np, gd, wl, emit=True):
     return line
 
 
+def timed_kernel(comp):
+    """Roofline fields naming the kernel that the launch timer of comp's last calls timed: the dense pass, or
+    in a layout small enough for the direct form the first of its passes."""
+    if comp.debug_state()[0][0]["form"] != 1:
+        return {"kernel": "k_dense"}
+    return {"kernel": "k_dacc",
+            "not_timed": "the direct form's three later passes, each of which reads every element again"}
+
+
 def oracle_quant_step_ok(np, o, idx, val, res, sign_bits, means, offsets, quant, columns=None):
     """One quantised call against the oracle's: sent indices and values and sign bits bit-exact, centres
     within 1e-6 relative (fp64 sums in another order), dropped residuals bit-exact, and every kept
@@ -606,7 +615,7 @@ def main():
             "byte_model": "12 B/element + 8 B/kept element",
         },
         "roofline": {
-            "kernel": "k_dense",
+            **timed_kernel(comp),
             "bound": "hbm",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS,

@@ -300,7 +300,8 @@ gd_status gd_compress_static(const uint64_t* tensor_offsets, uint32_t num_tensor
 const char* gd_status_string(gd_status status);
 
 /*
- * Timing of the dense pass (the kernel that streams grad and residual).
+ * Timing of the dense pass (the kernel that streams grad and residual; in a
+ * layout small enough for the direct form the first of its four passes).
  * gd_profile_enable(ctx, every) with every >= 1 times the dense launches
  * numbered 0, every, 2 * every, ... from this call on (every = 1: all of
  * them); every = 0 turns timing off; a negative value is GD_ERR_ARG.  A

@@ -13,6 +13,22 @@ def test_bench_parses_and_imports():
     assert callable(bench.main) and callable(bench.cpu_baseline)
 
 
+def test_roofline_names_the_kernel_that_was_timed():
+    sys.path.insert(0, ROOT)
+    import bench
+
+    class Comp:
+        def __init__(self, form):
+            self.form = form
+
+        def debug_state(self):
+            return [{"form": self.form}], {}
+
+    assert bench.timed_kernel(Comp(2)) == {"kernel": "k_dense"} and bench.timed_kernel(Comp(3)) == {"kernel": "k_dense"}
+    direct = bench.timed_kernel(Comp(1))
+    assert direct["kernel"] == "k_dacc" and "three later passes" in direct["not_timed"]
+
+
 def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=60)
