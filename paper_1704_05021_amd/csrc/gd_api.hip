@@ -128,14 +128,15 @@ struct DenseTimer {
     }
 };
 
-// 1-bit quantisation of the sent list.  k_total is the host-known output size
-// (exact threshold), or under a sampled threshold the capacity, a bound the
-// device-side count stays within.
+// The column sums that the emitting kernel clears for the quantisation behind it.
 gd::ColSums col_sums(const gd_ctx* ctx, gd_quant quant) {
     if (quant != GD_QUANT_COLUMN_MEAN) return {};
     return {ctx->cols.csum, ctx->cols.ccnt, 2 * (uint64_t)ctx->cols.groups};
 }
 
+// 1-bit quantisation of the sent list.  k_total is the host-known output size
+// (exact threshold), or under a sampled threshold the capacity, a bound the
+// device-side count stays within.
 gd_status run_quant(gd_ctx* ctx, float* residual, bool per, uint32_t ppm, bool direct, bool sampled, gd_quant quant,
                     uint64_t k_total, const gd_sparse* out, hipStream_t st) {
     if (quant == GD_QUANT_NONE) return GD_OK;

@@ -27,7 +27,15 @@
 // consecutive.  k_dcollect leaves a record per piece; the emitting block of a
 // piece reads its segment's records, resolves the threshold among the bin's
 // keys and counts what the earlier pieces keep, so no pass over the data and
-// no device-wide atomics are needed between the 22-bit prefix and the sent list.
+// no device-wide atomics are needed between the 22-bit prefix and the sent list
+// (but for the counts per tensor under a global threshold).
+//
+// The line between the forms (kDirectMaxUnits) was drawn under one threshold over
+// an MLP; it holds over numbers of tensors and scopes too, evenly cut, direct
+// against candidate form, us a call: 0.3M elements, 1 tensor 25 / 54, 1,024 per
+// tensor 72 / 160, 10,000 per tensor 121 / 993; 6.2M, global 51 / 66 (1 tensor),
+// 72 / 73 (1,025), 84 / 703 (50,000); per tensor 58 / 68 (27), 84 / 100 (256),
+// 125 / 196 (1,024), 93 / 200 (1,025), 298 / 1,286 (10,000).
 
 #include <hip/hip_ext.h>
 
@@ -426,8 +434,8 @@ __device__ __forceinline__ void mark_end(const DirectArgs& a, uint64_t total) {
     atomicAdd(&a.tensor_counts[a.T - 1], p);
 }
 
-// A block takes one chunk; wave w of it the units [w UPW, (w + 1) UPW) of the
-// chunk, each as four rows of 256 elements, one 16-byte vector per lane.
+// A block takes one piece; wave w of it the units [w UPW, (w + 1) UPW) of the
+// piece's chunk, each as four rows of 256 elements, one 16-byte vector per lane.
 constexpr uint32_t kSmallPiece = 256;  // pieces of at most this many elements skip the LDS histogram
 
 template <int UPW>
@@ -435,12 +443,12 @@ struct Rows {
     f4 v[4 * UPW];
 };
 
-// First element of row i of this wave's unit j (past the gradient: >= N or a
-// wrapped value, which no piece holds).
+// This wave's unit j of chunk c (it may lie past the last one).
 template <int UPW>
 __device__ __forceinline__ uint32_t wave_unit(const DirectArgs& a, uint32_t c, int j) {
     return c * (kDirectThreads / kWave * UPW) + wave_index() * UPW + j;
 }
+// First element of this lane's vector in row i of unit u (it may lie past the last element).
 __device__ __forceinline__ uint32_t row_elem(uint32_t u, int i) { return u * kUnitLen + i * 256 + 4 * lane_id(); }
 
 // acc of the wave's elements: the residual, which holds it, or params - copy.

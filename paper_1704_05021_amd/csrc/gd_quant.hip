@@ -12,7 +12,8 @@
 //                  value of the call;
 //   column mean  : per column of each tensor's row-major matrix view.
 // Per-tensor and global sums are taken in fp64 in a fixed order (per
-// candidate tile, then tiles in order), so they are deterministic; column
+// candidate tile, then tiles in order; after the direct form per slice of the
+// sent list, then slices in order), so they are deterministic; column
 // sums are fp64 atomics over the sent entries (in LDS per slice, then once
 // per touched column).  The sent bits are packed LSB-first, 32 per word,
 // and residual[idx] becomes acc - centre.
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(kBlock) void k_means(QuantArgs q) {
 // After the direct form (exact thresholds only, no tile sums): the sums come
 // from the sent list itself.
 //
-// The first output slot of each tensor, where one block cannot do it on the
-// way (more than kMeansThreads tensors).
+// The first output slot of each tensor, where the sums are taken by slices or
+// one block of k_dmeans cannot find them on the way (kMeansLocalT tensors).
 constexpr int kMeansThreads = 1024;
 constexpr uint32_t kMeansLocalT = kMeansThreads - 1;
 // Sent entries that one block per tensor sums directly; more are summed per
