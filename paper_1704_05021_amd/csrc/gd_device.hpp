@@ -195,6 +195,21 @@ __device__ __forceinline__ uint32_t lane_below_value(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, false);
 }
 
+// The last t in [0, n) with base(t) <= j, of a nondecreasing base with base(0) <= j:
+// 64 probes a round.  All lanes of the wave call it.
+template <typename Base>
+__device__ __forceinline__ uint32_t wave_last_at_most(const Base& base, uint32_t n, uint32_t j) {
+    uint32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave;
+        const uint64_t p = lo + (uint64_t)lane_id() * step;
+        // probes rise with the lane, so those at most j form a prefix; lane 0's is one
+        lo += (popc64(ballot(p < hi && base((uint32_t)p) <= j)) - 1u) * step;
+        hi = hi - lo > step ? lo + step : hi;
+    }
+    return lo;
+}
+
 // v of the DPP source lane, both halves of the double moved with control
 // CTRL in the rows ROW_MASK enables; a lane with no source gets -0.0, the
 // identity of floating-point addition (x + -0.0 is x for every x, zeros too).

@@ -153,21 +153,6 @@ __device__ __forceinline__ void add_value(double v[4], float x) {
     }
 }
 
-// The last t in [0, n) with base(t) <= j, of a nondecreasing base with base(0) <= j:
-// 64 probes a round.  All lanes of the wave call it.
-template <typename Base>
-__device__ __forceinline__ uint32_t wave_last_at_most(const Base& base, uint32_t n, uint32_t j) {
-    uint32_t lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const uint32_t step = (hi - lo + kWave - 1) / kWave;
-        const uint64_t p = lo + (uint64_t)lane_id() * step;
-        // probes rise with the lane, so those at most j form a prefix; lane 0's is one
-        lo += (popc64(ballot(p < hi && base((uint32_t)p) <= j)) - 1u) * step;
-        hi = hi - lo > step ? lo + step : hi;
-    }
-    return lo;
-}
-
 // Sums of every slice of kQSlice sent entries: per tensor under the sign mean
 // (slice j and tensor t have record j + t: along the list either grows from
 // one pair to the next, so a tensor's records are consecutive), else over all.

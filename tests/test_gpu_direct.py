@@ -114,6 +114,49 @@ def test_sums_over_many_tensors(tensors, quant):
         check_case(g, np.zeros_like(g), off, drop, per, quant, comp=comp, what=f"T={tensors} per={per} drop={drop}")
 
 
+@pytest.mark.parametrize("run", [1, 2, 63, 64, 65, 66, 200], ids=lambda r: f"runs_of_{r}")
+def test_counts_of_crowded_tensors(run):
+    # one threshold over tensors that start together (all but the last empty): at
+    # the first element, at a unit's start, inside a unit (two runs in a row, then a
+    # tensor per element over three units), at the last element and past it
+    n = 10_000
+    off = [0] * run + [700] * run + [1024] * run + [1500] * run + [1501] * (run + 1) + list(range(3_000, 6_072))
+    off += [8191] * run + [n - 1] * run + [n] * run
+    rng = np.random.default_rng(run)
+    g = rng.normal(0, 1e-3, n).astype(np.float32)
+    comp = gd.Compressor(off)
+    for drop in (0.99, 0.5, 0.0):
+        check_case(g, np.zeros_like(g), off, drop, False, False, comp=comp, what=f"run={run} drop={drop}")
+
+
+@pytest.mark.parametrize("layout", ["empty_in_a_row", "one_element_each"])
+def test_crowded_tensors_cost_no_more_than_in_the_candidate_form(layout):
+    n, t = 6_144_000, 20_000
+    off = [0] + ([n // 2] * t if layout == "empty_in_a_row" else list(range(1, t))) + [n]
+    comp = gd.Compressor(off)
+    g = torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    out = comp.alloc_out(0.99)
+
+    def us(mode):
+        comp.debug_force_bracket(mode)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        times = []
+        for _ in range(9):
+            r = torch.zeros_like(g)
+            torch.cuda.synchronize()
+            ev[0].record()
+            comp.compress(g, r, 0.99, out=out)
+            ev[1].record()
+            torch.cuda.synchronize()
+            times.append(1e3 * ev[0].elapsed_time(ev[1]))
+        comp.debug_force_bracket(0)
+        return sorted(times)[4]
+
+    direct, candidates = us(0), us(5)
+    # about a half and a tenth; 44 and 1.5 times as long where a lane took one tensor after another
+    assert direct < 1.2 * candidates, f"{direct:.0f} us, candidate form {candidates:.0f} us"
+
+
 @pytest.mark.parametrize("debug", [0, 1], ids=["direct", "candidates"])
 def test_state_of_segments_that_keep_nothing(debug):
     # 50 entries at 99% drop, and an empty tensor: the state is this call's, not an
