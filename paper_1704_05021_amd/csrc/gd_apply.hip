@@ -271,7 +271,9 @@ __global__ __launch_bounds__(kBlock) void k_apply(ApplyArgs a) {
 // this kernel).  Each thread loads kApplyTileEntries entries of the tile at
 // once, for all clients together (entry e of the tile belongs to the last
 // client whose first entry in the tile is at or before e); a tile with more
-// entries takes further rounds.
+// entries takes further rounds, each with the turns of its own clients only
+// (with a turn of all 40 clients a round, 40 that push the same 47 rows of a
+// 37M shard took 261 us, in the scattered form 219; now 198).
 //
 // Tiles of 4,096 parameters (four 16-byte vectors per thread, 16.9 KB of
 // LDS) keep eight blocks per compute unit in flight, which streams faster on
@@ -404,8 +406,13 @@ __global__ __launch_bounds__(kApplyTileThreads) void k_apply_tile(ApplyArgs a) {
             for (int k = 0; k < kApplyTileEntries; ++k)
                 if (off[k] < len) val[k] = push_centre(a, starts, a.means[cl[k]], i_lo + off[k], bits[k] & 1u);
         }
-        for (uint32_t t = 0; t < C; ++t) {
-            if (t > 0) __syncthreads();  // the previous client's turn done
+        // turns of the clients that the round's entries belong to only (the same in every
+        // wave: rounds of a tile with many entries hold few clients each)
+        const uint32_t e1 = total - e0 > kApplyTileRound ? e0 + kApplyTileRound - 1u : total - 1u;
+        const uint32_t c0 = popc64(ballot((uint32_t)lane < C && base <= e0)) - 1u;
+        const uint32_t c1 = popc64(ballot((uint32_t)lane < C && base <= e1)) - 1u;
+        for (uint32_t t = c0; t <= c1; ++t) {
+            if (t > c0) __syncthreads();  // the previous client's turn done
 #pragma unroll
             for (int k = 0; k < kApplyTileEntries; ++k) {
                 if (cl[k] != t || off[k] >= len) continue;
@@ -521,7 +528,7 @@ hipError_t launch_apply(const ApplyArgs& a, uint32_t max_nnz, hipStream_t st) {
     // With more clients streaming costs a turn of barriers more for each, and
     // evenly the two measure alike at the lines below (16 clients: 9.7M, per 100:
     // 25 / 29, per 50: 28 / 28; 37M, per 50: 50 / 57, per 30: 82 / 59; in the first
-    // rows 9.7M, per 100: 3157 / 487; 37M, per 30: 3942 / 500).
+    // rows 9.7M, per 100: 1439 / 404; 37M, per 30: 1968 / 413).
     const int form = g_apply_form.load();
     const bool aligned = (reinterpret_cast<uintptr_t>(a.p) & 15u) == 0;
     const bool cached = a.n <= (1u << 24);  // the shard stays in the caches (64 MiB)
