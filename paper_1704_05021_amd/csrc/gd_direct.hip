@@ -32,10 +32,10 @@
 //
 // The line between the forms (kDirectMaxUnits) was drawn under one threshold over
 // an MLP; it holds over numbers of tensors and scopes too, evenly cut, direct
-// against candidate form, us a call: 0.3M elements, 1 tensor 25 / 54, 1,024 per
-// tensor 72 / 160, 10,000 per tensor 121 / 993; 6.2M, global 51 / 66 (1 tensor),
-// 72 / 73 (1,025), 84 / 703 (50,000); per tensor 58 / 68 (27), 84 / 100 (256),
-// 125 / 196 (1,024), 93 / 200 (1,025), 298 / 1,286 (10,000).
+// against candidate form, us a call: 0.3M elements, 1 tensor 24 / 52, 1,024 per
+// tensor 71 / 159, 10,000 per tensor 119 / 983; 6.2M, global 51 / 69 (1 tensor),
+// 72 / 75 (1,025), 75 / 721 (50,000); per tensor 58 / 71 (27), 83 / 101 (256),
+// 123 / 196 (1,024), 92 / 197 (1,025), 294 / 1,285 (10,000).
 
 #include <hip/hip_ext.h>
 
