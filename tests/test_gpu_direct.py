@@ -172,3 +172,37 @@ def test_state_of_segments_that_keep_nothing(debug):
     for s in segs[:2]:
         assert (s["thr"], s["need"], s["zero"], s["miss"], s["clo"]) == (0xFFFFFFFF, 0, 0, 0, 0), s
     assert segs[2]["thr"] not in (0, 0xFFFFFFFF) and segs[2]["zero"] == 0
+
+
+@pytest.mark.parametrize("quant", [gd.GD_QUANT_NONE, gd.GD_QUANT_SIGN_MEAN, gd.GD_QUANT_COLUMN_MEAN],
+                         ids=["plain", "sign_mean", "column_mean"])
+def test_captured_call(quant):
+    # replayed with other calls on the same context between the replays
+    rng = np.random.default_rng(quant)
+    off = [0, 1_000, 1_000, 60_000, 90_001]
+    n = off[-1]
+    comp = gd.Compressor(off)
+    comp.set_columns([10, 1, 100, 1])
+    g = rng.normal(0, 1e-3, n).astype(np.float32)
+    gt, rt = torch.from_numpy(g).cuda(), torch.zeros(n, device="cuda")
+    out = comp.alloc_out(0.99, quant=quant)
+    r2 = torch.zeros(n, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        comp.compress(gt, rt, 0.99, quant=quant, out=out)
+    for step in range(5):
+        r = rt.cpu().numpy()
+        graph.replay()
+        torch.cuda.synchronize()
+        o = oracle.compress(g, r, off, 0.99, per_tensor=False, quant=quant, columns=[10, 1, 100, 1])
+        k = o.idx.size
+        assert out.k == k
+        assert np.array_equal(out.idx[:k].cpu().numpy().view(np.uint32), o.idx), step
+        assert np.array_equal(out.val[:k].cpu().numpy().view(np.uint32), o.val.view(np.uint32)), step
+        assert np.array_equal(out.tensor_counts.cpu().numpy().view(np.uint32), o.tensor_counts), step
+        # centres are fp64 sums in another order, rounded to binary32: the residual of a
+        # sent entry is off by the centre's rounding, 2^-23 of at most 1e-2
+        np.testing.assert_allclose(rt.cpu().numpy(), o.residual, rtol=0, atol=0 if not quant else 2.0 ** -23 * 1e-2)
+        comp.compress(gt, r2, 0.5, per_tensor=True, quant=quant)
+        comp.compress_sampled(gt, r2, 0.9, sample_ppm=100_000, quant=quant)

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 from paper_1704_05021_amd import gd, workloads as wl
-from parity import Result, assert_parity
+from parity import Result, assert_parity, check_case
 
 pytestmark = pytest.mark.gpu
 
@@ -312,3 +312,21 @@ def test_column_centres_under_a_large_capacity(capacity):
     for per, drop in ((False, 0.99), (True, 0.9), (False, 0.0)):
         check(g, r, offsets, drop, per, 10_000, 3, capacity=capacity, comp=comp, quant=gd.GD_QUANT_COLUMN_MEAN,
               columns=cols, what=f"capacity={capacity} per={per} drop={drop}")
+
+
+@pytest.mark.parametrize("n", [30_000, 6_400_000], ids=["direct", "candidates"])
+def test_calls_in_turn_with_the_exact_threshold(n):
+    """One context takes sampled calls and exact ones in turn, in both scopes and at
+    drop ratios that keep everything and nothing: they share histograms, which each
+    must find clear."""
+    rng = np.random.default_rng(n)
+    off = [0, 5, 5, n // 3, n // 3 + 4_097, n]
+    comp = gd.Compressor(off)
+    g, r = _values(rng, n, "gauss"), _values(rng, n, "gauss")
+    for i, drop in enumerate((0.99, 1.0, 0.5, 0.0, 0.99)):
+        for per in (False, True):
+            what = f"call {i} drop={drop} per={per}"
+            check(g, r, off, drop, per, 20_000, i, comp=comp, what=what)
+            check_case(g, r, off, drop, per, gd.GD_QUANT_SIGN_MEAN, comp=comp, what=what + " exact")
+            check(g, r, off, 0.9, not per, 1_000_000, i, comp=comp, what=what + " whole sample")
+            check_case(g, r, off, drop, not per, False, comp=comp, debug_bracket=i % 2 * 5, what=what + " exact, other scope")
